@@ -195,11 +195,8 @@ hipError_t launch_chan_totals(const float* partial, const Geo& g, RedGrid rg, in
 
 // ---- timestep embedding, weights, copies (misc.hip) ----------------------
 
-// e[b][o] = bias_a[o] + bias_b[o] + sum_d Wl[o][d] * SiLU(temb[b][d])
-hipError_t launch_temb_fwd(const void* temb, int dtype, int B, int D, int O, const float* Wl,
-                           const float* bias_a, const float* bias_b, float* e,
-                           hipStream_t st);
-// The projections of several stage blocks from one temb in one launch:
+// e[b][o] = bias_a[o] + bias_b[o] + sum_d Wl[o][d] * SiLU(temb[b][d]), the
+// projections of several stage blocks from one temb in one launch:
 // blk[k].e[b][o] (row stride ldE) for every block k < n; copy (null: none)
 // receives temb itself.
 constexpr int TEMB_MAX_BLOCKS = 16;
@@ -222,21 +219,43 @@ hipError_t launch_temb_bwd(const float* de, const void* temb, int dtype, int B, 
                            const float* Wl, float* dWl, float* dbl, float* db1, float* dtemb,
                            hipStream_t st);
 
-// dst[r][col_off + c] = (dtype) src[r][c] for r < rows, c < cols.
-hipError_t launch_convert_rows(const float* src, int rows, int cols, void* dst, int ldd,
-                               int col_off, int dtype, hipStream_t st);
-// 3x3 data-gradient weights: dst[c][8 - tap][o] = src[o][tap][c].
-hipError_t launch_flip3x3(const float* src, int O, int C, void* dst, int dtype,
-                          hipStream_t st);
-// dst[c][o] = src[o][c]
-hipError_t launch_transpose(const float* src, int O, int C, void* dst, int dtype,
-                            hipStream_t st);
-// dst[i] = a[i] + (b ? b[i] : 0)
-hipError_t launch_vec_add(const float* a, const float* b, float* dst, int n, hipStream_t st);
+// Refresh of a stage's weight copies from the fp32 masters: the jobs of one
+// list run in one launch (several when the table is full).
+constexpr int REFRESH_MAX_JOBS = 32;
+struct RefreshJob {
+  const float* src;   // [O][taps * C]
+  const float* src2;  // vector jobs: second addend or null
+  void* row;          // row[o * ldd + coff + k] in the compute dtype
+  void* tr;           // tr[(c * taps + taps - 1 - t) * O + o]
+  int O, C, taps;     // taps 0: an fp32 vector job of O elements
+  int ldd, coff;
+  int first;          // the job's first block
+};
+struct RefreshSet {
+  RefreshJob job[REFRESH_MAX_JOBS];
+  int n;
+};
+class RefreshList {
+ public:
+  RefreshList(int dtype, hipStream_t st) : dtype_(dtype), st_(st) { set_.n = 0; }
+  // row-major copy (at column coff of rows of ldd) and the data-gradient
+  // copy [c][taps - 1 - t][o] of an OHWI weight.  O % 8 == 0, C, ldd and
+  // coff % 4 == 0; src and tr 16-byte aligned, row 8-byte (bf16).
+  hipError_t weight(const float* src, int O, int C, int taps, void* row, int ldd, int coff,
+                    void* tr);
+  // dst[i] = a[i] + b[i] (a null vector counts as zeros)
+  hipError_t vec(const float* a, const float* b, float* dst, int n);
+  hipError_t flush();
+
+ private:
+  hipError_t add(RefreshJob job, long blocks);
+  int dtype_;
+  hipStream_t st_;
+  long blocks_ = 0;
+  RefreshSet set_;
+};
 // dst = (ddt)(a + b) elementwise, a of dtype adt, b fp32
 hipError_t launch_add_cast(const void* a, int adt, const float* b, void* dst, int ddt, long n,
                            hipStream_t st);
-// dst = convert(src), n elements (dtypes as DType)
-hipError_t launch_cast(const void* src, int sdt, void* dst, int ddt, long n, hipStream_t st);
 
 }  // namespace pulse

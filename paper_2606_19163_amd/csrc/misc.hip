@@ -21,36 +21,6 @@ __device__ __forceinline__ void st_any(void* p, int dtype, long i, float v) {
     static_cast<float*>(p)[i] = v;
 }
 
-// one wave per (o, b): lanes stride over d (four loads in flight per lane),
-// xor-shuffle tree reduction
-__global__ __launch_bounds__(64) void k_temb_fwd(const void* temb, int dtype, int D, int O,
-                                                 const float* Wl, const float* bias_a,
-                                                 const float* bias_b, float* e) {
-  const int o = blockIdx.x, b = blockIdx.y;
-  const float* w = Wl + (long)o * D;
-  const long t0 = (long)b * D;
-  float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
-  int d = threadIdx.x;
-  for (; d + 192 < D; d += 256) {
-    const float w0 = w[d], w1 = w[d + 64], w2 = w[d + 128], w3 = w[d + 192];
-    const float x0 = ld_any(temb, dtype, t0 + d), x1 = ld_any(temb, dtype, t0 + d + 64);
-    const float x2 = ld_any(temb, dtype, t0 + d + 128), x3 = ld_any(temb, dtype, t0 + d + 192);
-    s0 += w0 * silu_f(x0);
-    s1 += w1 * silu_f(x1);
-    s2 += w2 * silu_f(x2);
-    s3 += w3 * silu_f(x3);
-  }
-  for (; d < D; d += 64) s0 += w[d] * silu_f(ld_any(temb, dtype, t0 + d));
-  float s = (s0 + s1) + (s2 + s3);
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-  if (threadIdx.x == 0) {
-    float bias = bias_a[o];
-    if (bias_b) bias += bias_b[o];
-    e[(long)b * O + o] = s + bias;
-  }
-}
-
 // Every block's projection of one stage half in one launch.  Block
 // (row tile, stage block k, image group) of 4 waves, each wave 2 rows o of
 // Wl_k for 8 images.  Per slice of d every memory read is issued at once:
@@ -275,43 +245,75 @@ __global__ __launch_bounds__(1024) void k_temb_bwd_x(const float* de, const void
   }
 }
 
-__global__ void k_convert_rows(const float* src, int rows, int cols, void* dst, int ldd,
-                               int col_off, int dtype) {
-  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (long)rows * cols) return;
-  const long r = i / cols;
-  const long c = i - r * cols;
-  st_any(dst, dtype, r * ldd + col_off + c, src[i]);
-}
+// Refresh of a stage's weight copies: one launch over a table of jobs, each
+// 64 x 64 tile of an fp32 master [O][taps * C] read once (16-byte loads,
+// coalesced) and written twice: the row-major compute copy straight from
+// registers, and the data-gradient copy dst[c][taps - 1 - t][o] through LDS,
+// so that its stores are 16-byte pieces of 8 consecutive o as well.  Bound
+// by HBM: 4 bytes read and 2 x 2 written per bf16 weight.  The 161 M
+// weights of a 1280-channel stage take 221-244 us in one launch (5.3-5.8
+// TB/s); one kernel per copy with one element per thread, which read the
+// master twice and, for the transposed copies, in strides of a whole row,
+// took 1384 us in 26 launches.
+// LDS rows of 65 floats: the 16-lane row pieces of the stores and the
+// 8-row column pieces of the reads both touch 64 different banks.
+constexpr int RF_T = 64;
 
-__global__ void k_flip3x3(const float* src, int O, int C, void* dst, int dtype) {
-  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (long)O * 9 * C) return;
-  // destination index (c, t, o)
-  const int o = (int)(i % O);
-  const long ct = i / O;
-  const int t = (int)(ct % 9);
-  const int c = (int)(ct / 9);
-  st_any(dst, dtype, i, src[((long)o * 9 + (8 - t)) * C + c]);
-}
-
-__global__ void k_transpose(const float* src, int O, int C, void* dst, int dtype) {
-  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (long)O * C) return;
-  const int o = (int)(i % O);
-  const int c = (int)(i / O);
-  st_any(dst, dtype, i, src[(long)o * C + c]);
-}
-
-__global__ void k_vec_add(const float* a, const float* b, float* dst, int n) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) dst[i] = a[i] + (b ? b[i] : 0.f);
-}
-
-__global__ void k_cast(const void* src, int sdt, void* dst, int ddt, long n) {
-  for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (long)gridDim.x * blockDim.x)
-    st_any(dst, ddt, i, ld_any(src, sdt, i));
+template <int DT>
+__global__ __launch_bounds__(256) void k_refresh(RefreshSet set) {
+  __shared__ float sm[RF_T][RF_T + 1];
+  int j = 0;
+  while (j + 1 < set.n && (int)blockIdx.x >= set.job[j + 1].first) ++j;
+  const RefreshJob& job = set.job[j];
+  const int tile = (int)blockIdx.x - job.first;
+  const int t = threadIdx.x;
+  if (job.taps == 0) {  // fp32 vector: row = src + src2 (null: zero)
+    const int i = tile * 256 + t;
+    if (i < job.O)
+      static_cast<float*>(job.row)[i] =
+          (job.src ? job.src[i] : 0.f) + (job.src2 ? job.src2[i] : 0.f);
+    return;
+  }
+  const int K = job.taps * job.C;
+  const int tk = (K + RF_T - 1) / RF_T;
+  const int o0 = tile / tk * RF_T, k0 = (tile - tile / tk * tk) * RF_T;
+  const int kq = (t & 15) * 4;  // this thread's 4 columns
+  float4 v[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int o = o0 + (t >> 4) + 16 * i;
+    v[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (o < job.O && k0 + kq < K)
+      v[i] = *reinterpret_cast<const float4*>(job.src + (long)o * K + k0 + kq);
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int r = (t >> 4) + 16 * i;
+    sm[r][kq] = v[i].x;
+    sm[r][kq + 1] = v[i].y;
+    sm[r][kq + 2] = v[i].z;
+    sm[r][kq + 3] = v[i].w;
+    if (o0 + r < job.O && k0 + kq < K) {
+      const long e = (long)(o0 + r) * job.ldd + job.coff + k0 + kq;
+      if constexpr (DT == DT_BF16)
+        *reinterpret_cast<uint2*>(static_cast<uint16_t*>(job.row) + e) =
+            make_uint2(pack2(v[i].x, v[i].y), pack2(v[i].z, v[i].w));
+      else
+        *reinterpret_cast<float4*>(static_cast<float*>(job.row) + e) = v[i];
+    }
+  }
+  __syncthreads();
+  const int oc = (t & 7) * 8;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int kk = (t >> 3) + 32 * i;
+    if (k0 + kk >= K || o0 + oc >= job.O) continue;
+    const int tap = (k0 + kk) / job.C, c = k0 + kk - tap * job.C;
+    float w[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) w[q] = sm[oc + q][kk];
+    st8(job.tr, DT, job.O, (long)c * job.taps + job.taps - 1 - tap, o0 + oc, w);
+  }
 }
 
 // dst = (ddt) (a + b), a of dtype adt, b fp32
@@ -338,17 +340,7 @@ __global__ __launch_bounds__(256) void k_add_cast8(const void* a, const float* b
   }
 }
 
-unsigned nblk(long n, int t = 256) { return (unsigned)((n + t - 1) / t); }
-
 }  // namespace
-
-hipError_t launch_temb_fwd(const void* temb, int dtype, int B, int D, int O, const float* Wl,
-                           const float* bias_a, const float* bias_b, float* e,
-                           hipStream_t st) {
-  hipLaunchKernelGGL(k_temb_fwd, dim3(O, B), dim3(64), 0, st, temb, dtype, D, O, Wl, bias_a,
-                     bias_b, e);
-  return hipGetLastError();
-}
 
 hipError_t launch_temb_fwd_multi(const void* temb, int dtype, int B, int D,
                                  const TembFwdSet& set, void* copy, hipStream_t st) {
@@ -378,38 +370,48 @@ hipError_t launch_temb_bwd(const float* de, const void* temb, int dtype, int B, 
   return hipGetLastError();
 }
 
-hipError_t launch_convert_rows(const float* src, int rows, int cols, void* dst, int ldd,
-                               int col_off, int dtype, hipStream_t st) {
-  hipLaunchKernelGGL(k_convert_rows, dim3(nblk((long)rows * cols)), dim3(256), 0, st, src, rows,
-                     cols, dst, ldd, col_off, dtype);
+hipError_t RefreshList::flush() {
+  if (set_.n == 0) return hipSuccess;
+  auto kern = dtype_ == DT_BF16 ? k_refresh<DT_BF16> : k_refresh<DT_F32>;
+  hipLaunchKernelGGL(kern, dim3((unsigned)blocks_), dim3(256), 0, st_, set_);
+  set_.n = 0;
+  blocks_ = 0;
   return hipGetLastError();
 }
 
-hipError_t launch_flip3x3(const float* src, int O, int C, void* dst, int dtype,
-                          hipStream_t st) {
-  hipLaunchKernelGGL(k_flip3x3, dim3(nblk((long)O * 9 * C)), dim3(256), 0, st, src, O, C, dst,
-                     dtype);
-  return hipGetLastError();
+hipError_t RefreshList::add(RefreshJob job, long blocks) {
+  hipError_t e = hipSuccess;
+  // a table or a grid that is full goes first
+  if (set_.n == REFRESH_MAX_JOBS || (long)blocks_ + blocks > 0x7fffffffL) e = flush();
+  job.first = (int)blocks_;
+  set_.job[set_.n++] = job;
+  blocks_ += blocks;
+  return e;
 }
 
-hipError_t launch_transpose(const float* src, int O, int C, void* dst, int dtype,
-                            hipStream_t st) {
-  hipLaunchKernelGGL(k_transpose, dim3(nblk((long)O * C)), dim3(256), 0, st, src, O, C, dst,
-                     dtype);
-  return hipGetLastError();
+hipError_t RefreshList::weight(const float* src, int O, int C, int taps, void* row, int ldd,
+                               int coff, void* tr) {
+  if (O % 8 || C % 4 || ldd % 4 || coff % 4) return hipErrorInvalidValue;
+  RefreshJob j{};
+  j.src = src;
+  j.row = row;
+  j.tr = tr;
+  j.O = O;
+  j.C = C;
+  j.taps = taps;
+  j.ldd = ldd;
+  j.coff = coff;
+  const long K = (long)taps * C;
+  return add(j, ((O + RF_T - 1) / RF_T) * ((K + RF_T - 1) / RF_T));
 }
 
-hipError_t launch_vec_add(const float* a, const float* b, float* dst, int n, hipStream_t st) {
-  hipLaunchKernelGGL(k_vec_add, dim3(nblk(n)), dim3(256), 0, st, a, b, dst, n);
-  return hipGetLastError();
-}
-
-hipError_t launch_cast(const void* src, int sdt, void* dst, int ddt, long n, hipStream_t st) {
-  long b = (n + 255) / 256;
-  if (b > 8192) b = 8192;
-  if (b < 1) b = 1;
-  hipLaunchKernelGGL(k_cast, dim3((unsigned)b), dim3(256), 0, st, src, sdt, dst, ddt, n);
-  return hipGetLastError();
+hipError_t RefreshList::vec(const float* a, const float* b, float* dst, int n) {
+  RefreshJob j{};
+  j.src = a;
+  j.src2 = b;
+  j.row = dst;
+  j.O = n;
+  return add(j, (n + 255) / 256);
 }
 
 hipError_t launch_add_cast(const void* a, int adt, const float* b, void* dst, int ddt, long n,

@@ -1519,23 +1519,21 @@ pulse_status pulse_stage_sync_params(pulse_stage* s, void* stream) {
   hipStream_t st = static_cast<hipStream_t>(stream);
   pulse_status ps;
   if ((ps = order_after_last(s, st)) != PULSE_OK) return ps;
-  const int dt = s->dtype;
+  RefreshList rl(s->dtype, st);
   for (auto* v : {&s->eb, &s->db})
     for (auto& b : *v) {
-      HIPCHK(launch_convert_rows(s->pp(b.W1), b.cout, 9 * b.cin, s->ws + b.wf1, 9 * b.cin, 0, dt,
-                                 st));
-      HIPCHK(launch_convert_rows(s->pp(b.W2), b.cout, 9 * b.cout, s->ws + b.wf2, b.ldb2, 0, dt,
-                                 st));
+      HIPCHK(rl.weight(s->pp(b.W1), b.cout, b.cin, 9, s->ws + b.wf1, 9 * b.cin, 0,
+                       s->ws + b.wd1));
+      HIPCHK(rl.weight(s->pp(b.W2), b.cout, b.cout, 9, s->ws + b.wf2, b.ldb2, 0,
+                       s->ws + b.wd2));
       if (b.conv_sc)
-        HIPCHK(launch_convert_rows(s->pp(b.Ws), b.cout, b.cin, s->ws + b.wf2, b.ldb2,
-                                   9 * b.cout, dt, st));
-      HIPCHK(launch_flip3x3(s->pp(b.W1), b.cout, b.cin, s->ws + b.wd1, dt, st));
-      HIPCHK(launch_flip3x3(s->pp(b.W2), b.cout, b.cout, s->ws + b.wd2, dt, st));
-      if (b.conv_sc) HIPCHK(launch_transpose(s->pp(b.Ws), b.cout, b.cin, s->ws + b.wsd, dt, st));
-      HIPCHK(launch_vec_add(s->pp(b.b2), b.conv_sc ? s->pp(b.bs) : nullptr,
-                            reinterpret_cast<float*>(s->ws + b.bias2), b.cout, st));
+        HIPCHK(rl.weight(s->pp(b.Ws), b.cout, b.cin, 1, s->ws + b.wf2, b.ldb2, 9 * b.cout,
+                         s->ws + b.wsd));
+      HIPCHK(rl.vec(s->pp(b.b2), b.conv_sc ? s->pp(b.bs) : nullptr,
+                    reinterpret_cast<float*>(s->ws + b.bias2), b.cout));
     }
-  HIPCHK(hipMemsetAsync(s->scratch(s->s_zero), 0, 256, st));
+  HIPCHK(rl.vec(nullptr, nullptr, s->sf(s->s_zero), 64));
+  HIPCHK(rl.flush());
   if ((ps = mark_last(s, st)) != PULSE_OK) return ps;
   s->synced = true;
   return PULSE_OK;

@@ -908,22 +908,18 @@ pulse_status pulse_tstage_sync_params(pulse_tstage* s, void* stream) {
   hipStream_t st = static_cast<hipStream_t>(stream);
   TCHK(tsettle(s, st, true));
   const int C = s->C, R = s->R;
+  RefreshList rl(DT_BF16, st);
   for (auto* v : {&s->eb, &s->db})
     for (const TBlock& b : *v) {
-      THIP(launch_convert_rows(s->pp(b.qkvW), 3 * C, C, s->at(b.w_qkv), C, 0, DT_BF16, st));
-      THIP(launch_transpose(s->pp(b.qkvW), 3 * C, C, s->at(b.t_qkv), DT_BF16, st));
-      THIP(launch_convert_rows(s->pp(b.projW), C, C, s->at(b.w_proj), C, 0, DT_BF16, st));
-      THIP(launch_transpose(s->pp(b.projW), C, C, s->at(b.t_proj), DT_BF16, st));
-      THIP(launch_convert_rows(s->pp(b.fc1W), R, C, s->at(b.w_fc1), C, 0, DT_BF16, st));
-      THIP(launch_transpose(s->pp(b.fc1W), R, C, s->at(b.t_fc1), DT_BF16, st));
-      THIP(launch_convert_rows(s->pp(b.fc2W), C, R, s->at(b.w_fc2), R, 0, DT_BF16, st));
-      THIP(launch_transpose(s->pp(b.fc2W), C, R, s->at(b.t_fc2), DT_BF16, st));
-      if (b.dec) {
-        THIP(launch_convert_rows(s->pp(b.skW), C, 2 * C, s->at(b.w_sk), 2 * C, 0, DT_BF16, st));
-        THIP(launch_transpose(s->pp(b.skW), C, 2 * C, s->at(b.t_sk), DT_BF16, st));
-      }
+      THIP(rl.weight(s->pp(b.qkvW), 3 * C, C, 1, s->at(b.w_qkv), C, 0, s->at(b.t_qkv)));
+      THIP(rl.weight(s->pp(b.projW), C, C, 1, s->at(b.w_proj), C, 0, s->at(b.t_proj)));
+      THIP(rl.weight(s->pp(b.fc1W), R, C, 1, s->at(b.w_fc1), C, 0, s->at(b.t_fc1)));
+      THIP(rl.weight(s->pp(b.fc2W), C, R, 1, s->at(b.w_fc2), R, 0, s->at(b.t_fc2)));
+      if (b.dec)
+        THIP(rl.weight(s->pp(b.skW), C, 2 * C, 1, s->at(b.w_sk), 2 * C, 0, s->at(b.t_sk)));
     }
-  THIP(hipMemsetAsync(s->at(s->s_zero), 0, 256, st));
+  THIP(rl.vec(nullptr, nullptr, s->fat(s->s_zero), 64));
+  THIP(rl.flush());
   s->synced = true;
   return PULSE_OK;
 }
