@@ -37,7 +37,7 @@ CFLAGS = [
     "-I", CSRC,
 ]
 
-SOURCES = ["igemm.hip", "igemm2.hip", "norm.hip", "misc.hip", "probe.hip", "attn.hip",
+SOURCES = ["igemm2.hip", "norm.hip", "misc.hip", "probe.hip", "attn.hip",
            "tnorm.hip", "stage.cpp", "tstage.cpp", "sched.cpp", "partition.cpp"]
 
 # Attention's softmax takes maxima of MFMA results: with the IEEE mode bit

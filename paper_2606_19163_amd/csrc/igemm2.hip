@@ -54,18 +54,39 @@ __device__ __forceinline__ void wait_vmcnt() {
 }
 
 
+// wait until at most `after` (0..MAX) stages of NU loads are in flight
+template <int MAX, int NU>
+__device__ __forceinline__ void wait_stages(int after) {
+  if constexpr (MAX <= 0) {
+    wait_vmcnt<0>();
+  } else {
+    if (after >= MAX)
+      wait_vmcnt<MAX * NU>();
+    else
+      wait_stages<MAX - 1, NU>(after);
+  }
+}
+
 }  // namespace
 
-template <int BM_, int BN_, int WM_, int WN_, int STAGES_ = 2, int BK_ = 64>
+// F32_: fp32 operands (v_mfma_f32_16x16x4_f32), else bf16.  Everything up
+// to the MFMA moves 16-byte chunks, so one row of a tile is BK bf16 or BK
+// fp32 values and a fragment is 16 bytes per lane either way: 8 bf16 k
+// values of one MFMA, or one fp32 k value of each of four.
+template <int BM_, int BN_, int WM_, int WN_, int STAGES_ = 2, int BK_ = 64, bool F32_ = false,
+          bool RDF_ = true>
 struct CfgC {
+  static constexpr bool RDF = RDF_;
+  static constexpr bool F32 = F32_;
+  static constexpr int ESZ = F32 ? 4 : 2;     // bytes per element
   static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, BK = BK_, STAGES = STAGES_;
   static constexpr int WAVES_M = BM / WM, WAVES_N = BN / WN, NW = WAVES_M * WAVES_N;
   static constexpr int NT = NW * 64;
   static constexpr int TM = WM / 16, TN = WN / 16;
-  static constexpr int RB = BK * 2;           // row bytes
+  static constexpr int RB = BK * ESZ;         // row bytes
   static constexpr int CPR = RB / 16;         // 16-byte chunks per row
   static constexpr int RPL = 1024 / RB;       // rows per 1 KB wave load
-  static constexpr int KH = BK / 32;          // MFMA K-steps (32) per stage
+  static constexpr int KH = RB / 64;          // 64-byte fragment columns per stage
   static constexpr int A_BYTES = BM * RB, B_BYTES = BN * RB;
   static constexpr int STAGE = A_BYTES + B_BYTES;
   static constexpr int WLA = A_BYTES / 1024, WLB = B_BYTES / 1024, WL = WLA + WLB;
@@ -75,10 +96,10 @@ struct CfgC {
   static constexpr int UA = WLA / NW;  // loads u < UA fill A, the rest fill B
   static constexpr int LDC = BN + 4;
   static constexpr int LDS_BYTES = STAGES * STAGE;
-  static_assert(BK == 32 || BK == 64, "K-step");
-  static_assert(STAGES >= 2 && STAGES <= 4, "stages");
+  static_assert(RB == 64 || RB == 128, "K-step");
+  static_assert(STAGES >= 2 && (STAGES - 2) * NU < 64, "vmcnt");
   static_assert(16 * LDC * 4 <= STAGES * STAGE, "epilogue slice must fit the stages");
-  static_assert((2 * 16 * LDC + 4 * BN) * 4 <= STAGES * STAGE,
+  static_assert(F32 || (2 * 16 * LDC + 4 * BN) * 4 <= STAGES * STAGE,
                 "GroupNorm-backward slices and constants must fit the stages");
   static_assert(STAGES * STAGE <= 160 * 1024, "LDS");
   static_assert(A_BYTES % 1024 == 0 && B_BYTES % 1024 == 0, "whole wave loads");
@@ -135,20 +156,25 @@ constexpr int best_rot(int P) {  // a + 256 * b of the first conflict-free pair
   return best;
 }
 
-template <int BM_, int BN_, int WM_, int WN_>
+template <int BM_, int BN_, int WM_, int WN_, bool F32_ = false>
 struct CfgW {
+  static constexpr bool F32 = F32_;
+  static constexpr int ESZ = F32 ? 4 : 2;     // bytes per element
+  static constexpr int EPC = 16 / ESZ;        // elements per 16-byte chunk
   static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, BK = 64;
   static constexpr int WAVES_M = BM / WM, WAVES_N = BN / WN, NW = WAVES_M * WAVES_N;
   static constexpr int NT = NW * 64;
   static constexpr int TM = WM / 16, TN = WN / 16;
-  static constexpr int PA = BM * 2, PB = BN * 2;  // row pitch (bytes): one pixel
-  static constexpr int CA = BM / 8, CB = BN / 8;  // 16-byte chunks per row
+  static constexpr int PA = BM * ESZ, PB = BN * ESZ;  // row pitch (bytes): one pixel
+  static constexpr int CA = PA / 16, CB = PB / 16;    // 16-byte chunks per row
   static constexpr int A_BYTES = BK * PA, B_BYTES = BK * PB;
   static constexpr int STAGE = A_BYTES + B_BYTES;
   static constexpr int WLA = A_BYTES / 1024, WLB = B_BYTES / 1024, WL = WLA + WLB;
   static constexpr int NU = WL / NW;
   static constexpr int UA = WLA / NW;  // loads u < UA fill A, the rest fill B
-  static constexpr int RA = best_rot(PA), RB = best_rot(PB);
+  // fp32 fragments are one value per lane: 16 channels of the 4 pixel rows
+  // r & 3 = 0..3, which a rotation by 64 bytes per row puts in 64 banks
+  static constexpr int RA = F32 ? 2 : best_rot(PA), RB = F32 ? 2 : best_rot(PB);
   static constexpr int RA_A = RA % 256, RA_B = RA / 256, RB_A = RB % 256, RB_B = RB / 256;
   static constexpr int LDC = BN + 4;
   static constexpr int LDS_BYTES = 2 * STAGE;
@@ -158,7 +184,9 @@ struct CfgW {
                     (BK * PB) % 1024 == 0,
                 "loads");
   static_assert(BM % 16 == 0 && BN % 16 == 0, "rows of whole 32-byte units");
-  static_assert(36 * PA < 65536 && A_BYTES + 36 * PB < 65536, "read offsets are immediates");
+  static_assert((F32 ? 60 : 36) * PA < 65536 && A_BYTES + (F32 ? 60 : 36) * PB < 65536,
+                "read offsets are immediates");
+  static_assert(!F32 || (PA % 256 == 0 && PB % 256 == 0), "fp32 rows cover whole bank periods");
   static_assert(WM % 16 == 0 && WN % 16 == 0, "tile");
 };
 
@@ -247,12 +275,13 @@ struct SegRt {
   int c0, C, taps, begin;
 };
 
+template <int ESZ>
 __device__ __forceinline__ SegRt seg_rt(const Seg& g, long P) {
   SegRt s;
-  s.r0 = make_rsrc(g.in.s0.ptr, P * g.in.s0.C * 2);
-  s.r1 = make_rsrc(g.in.s1.ptr, P * g.in.s1.C * 2);
-  s.pitch0 = (uint32_t)(g.in.s0.C * 2);
-  s.pitch1 = (uint32_t)(g.in.s1.C * 2);
+  s.r0 = make_rsrc(g.in.s0.ptr, P * g.in.s0.C * ESZ);
+  s.r1 = make_rsrc(g.in.s1.ptr, P * g.in.s1.C * ESZ);
+  s.pitch0 = (uint32_t)(g.in.s0.C * ESZ);
+  s.pitch1 = (uint32_t)(g.in.s1.C * ESZ);
   s.c0 = g.in.c0;
   s.C = g.C;
   s.taps = g.taps;
@@ -270,6 +299,27 @@ __device__ __forceinline__ void select_into(SegRt& d, bool c, const SegRt& a, co
   d.C = c ? a.C : b.C;
   d.taps = c ? a.taps : b.taps;
   d.begin = c ? a.begin : b.begin;
+}
+
+// acc += A B^T of one fragment column (see CfgC): one bf16 MFMA per tile, or
+// four fp32 ones, whose k values go round the tiles (the MFMAs of one
+// accumulator in a row would wait for each other)
+template <bool F32, int TM, int TN>
+__device__ __forceinline__ void mfma_frags(const bf16x8_t (&a)[TM], const bf16x8_t (&b)[TN],
+                                           f32x4_t (&acc)[TM][TN]) {
+#pragma unroll
+  for (int e = 0; e < (F32 ? 4 : 1); ++e)
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        if constexpr (F32)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(__builtin_bit_cast(f32x4_t, a[i])[e],
+                                                           __builtin_bit_cast(f32x4_t, b[j])[e],
+                                                           acc[i][j], 0, 0, 0);
+        else
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+      }
 }
 
 // Stage the accumulator rows [i*16, i*16+16) of every wave of row group g
@@ -376,22 +426,22 @@ __global__ __launch_bounds__(C::NT) void igemm2_conv(GemmArgs a) {
     } else if (wl < C::WL) {
       const int r = (wl - C::WLA) * C::RPL + lane / C::CPR;
       const int n = n0 + r;
-      coff[u] = n < a.N ? (uint32_t)n * (uint32_t)(a.ldb * 2) +
+      coff[u] = n < a.N ? (uint32_t)n * (uint32_t)(a.ldb * C::ESZ) +
                               (uint32_t)(((lane % C::CPR) ^ swz_row<C::RB>(r)) * 16)
                         : OOB;
     }
   }
 
-  const SegRt q1 = seg_rt(a.seg[1], P);
-  const SegRt q2 = seg_rt(a.seg[2], P);
-  const __amdgpu_buffer_rsrc_t rw = make_rsrc(a.Bw, (long)a.N * a.ldb * 2);
+  const SegRt q1 = seg_rt<C::ESZ>(a.seg[1], P);
+  const SegRt q2 = seg_rt<C::ESZ>(a.seg[2], P);
+  const __amdgpu_buffer_rsrc_t rw = make_rsrc(a.Bw, (long)a.N * a.ldb * C::ESZ);
   const uint32_t sbase = lds_u32(smem);
 
   // K position of the next stage to issue: segment, channel chunk and tap
   // (dy, dx), walked chunk-major (the taps of one 64-channel chunk run back
   // to back, so the shifted reads of one input slice stay in L2), without
   // divisions.  The weight column of (tap, channel c) is begin + tap*C + c.
-  SegRt cur = seg_rt(a.seg[0], P);
+  SegRt cur = seg_rt<C::ESZ>(a.seg[0], P);
   int iseg = 0, itap = 0, icb = 0, idy, idx;
   if (kt0 > 0) {
     int q = kt0;  // first K-step of this split
@@ -429,10 +479,10 @@ __global__ __launch_bounds__(C::NT) void igemm2_conv(GemmArgs a) {
     const bool second = icb >= cur.c0;
     const __amdgpu_buffer_rsrc_t rs = second ? cur.r1 : cur.r0;
     const uint32_t pitch = second ? cur.pitch1 : cur.pitch0;
-    const uint32_t cbyte = (uint32_t)((second ? icb - cur.c0 : icb) * 2);
+    const uint32_t cbyte = (uint32_t)((second ? icb - cur.c0 : icb) * C::ESZ);
     const int t9 = (idy + 1) * 3 + idx + 1;
     const int shift = idy * W + idx;
-    const uint32_t kbyte = (uint32_t)((cur.begin + itap * cur.C + icb) * 2);
+    const uint32_t kbyte = (uint32_t)((cur.begin + itap * cur.C + icb) * C::ESZ);
 #pragma unroll
     for (int u = 0; u < C::NU; ++u) {
       const int wl = wave + u * C::NW;
@@ -483,24 +533,30 @@ __global__ __launch_bounds__(C::NT) void igemm2_conv(GemmArgs a) {
     // stages issued after this one: min(STAGES - 2, KT - 1 - kt), each NU
     // (or NU_LO) loads of this wave
     const int after = min(C::STAGES - 2, KT - 1 - kt);
-    const bool hi = C::REM == 0 || wave < C::REM;
-    if (after <= 0)
-      wait_vmcnt<0>();
-    else if (after == 1)
-      hi ? wait_vmcnt<C::NU>() : wait_vmcnt<C::NU_LO>();
+    if (C::REM == 0 || wave < C::REM)
+      wait_stages<C::STAGES - 2, C::NU>(after);
     else
-      hi ? wait_vmcnt<2 * C::NU>() : wait_vmcnt<2 * C::NU_LO>();
+      wait_stages<C::STAGES - 2, C::NU_LO>(after);
     __builtin_amdgcn_s_barrier();
     const uint32_t sb = sbase + (uint32_t)(slot * C::STAGE);
+    if constexpr (!C::RDF) {
     // the slot refilled here was read one step ago: every wave is past that
     if (kt + C::STAGES - 1 < KT) {
       const int ns = slot + C::STAGES - 1;
       issue((uint32_t)((ns >= C::STAGES ? ns - C::STAGES : ns) * C::STAGE));
     }
+    }
 #pragma unroll
     for (int s = 0; s < C::KH; ++s) {
       ds_rd_n<C::TM, 16 * C::RB, 0>(af[s], sb + fa[s]);
       ds_rd_n<C::TN, 16 * C::RB, C::A_BYTES>(bfr[s], sb + fb[s]);
+    }
+    if constexpr (C::RDF) {
+    // the slot refilled here was read one step ago: every wave is past that
+    if (kt + C::STAGES - 1 < KT) {
+      const int ns = slot + C::STAGES - 1;
+      issue((uint32_t)((ns >= C::STAGES ? ns - C::STAGES : ns) * C::STAGE));
+    }
     }
     slot = slot + 1 == C::STAGES ? 0 : slot + 1;
 #pragma unroll
@@ -516,12 +572,7 @@ __global__ __launch_bounds__(C::NT) void igemm2_conv(GemmArgs a) {
       for (int i = 0; i < C::TM; ++i) tie(af[s][i]);
 #pragma unroll
       for (int j = 0; j < C::TN; ++j) tie(bfr[s][j]);
-#pragma unroll
-      for (int i = 0; i < C::TM; ++i)
-#pragma unroll
-        for (int j = 0; j < C::TN; ++j)
-          acc[i][j] =
-              __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[s][i], bfr[s][j], acc[i][j], 0, 0, 0);
+      mfma_frags<C::F32>(af[s], bfr[s], acc);
     }
     __builtin_amdgcn_sched_barrier(0);
   }
@@ -529,13 +580,14 @@ __global__ __launch_bounds__(C::NT) void igemm2_conv(GemmArgs a) {
 
   // epilogue in 16-row slices: accumulators -> LDS -> 8-channel rows
   // (+bias, +rowvec, +residual) -> 16-byte stores.  With a.stats the stored
-  // (bf16-rounded) values go back to the slice in LDS and thread t < BN adds
+  // (rounded to the stage dtype) values go back to the slice in LDS and thread t < BN adds
   // column t of every slice to its running sum and sum of squares: the
   // GroupNorm statistics of the output, one row per (image, M-tile).
   float* ct = reinterpret_cast<float*>(smem);
   constexpr int NV8 = C::BN / 8;
   constexpr int NTK = (16 * NV8 + C::NT - 1) / C::NT;  // tasks per thread and slice
   static_assert(C::BN <= C::NT, "one thread per output column for the statistics");
+  static_assert(!(GNB && C::F32), "the GroupNorm-backward sums read bf16 tensors");
   const bool stats = !GNB && a.stats != nullptr;
   const bool raw = !GNB && a.ksplit > 1;  // raw partial; the finalize adds the epilogue terms
   const bool has_res = !GNB && a.resid.s0.ptr != nullptr;
@@ -700,11 +752,13 @@ __global__ __launch_bounds__(C::NT) void igemm2_conv(GemmArgs a) {
           w2[1] = make_float4(dxv[4], dxv[5], dxv[6], dxv[7]);
         }
         if (stats) {
+          if constexpr (!C::F32) {
+#pragma unroll
+            for (int q = 0; q < 8; ++q) v[q] = bf2f(f2bf(v[q]));
+          }
           float4* w = reinterpret_cast<float4*>(src);
-          w[0] = make_float4(bf2f(f2bf(v[0])), bf2f(f2bf(v[1])), bf2f(f2bf(v[2])),
-                             bf2f(f2bf(v[3])));
-          w[1] = make_float4(bf2f(f2bf(v[4])), bf2f(f2bf(v[5])), bf2f(f2bf(v[6])),
-                             bf2f(f2bf(v[7])));
+          w[0] = make_float4(v[0], v[1], v[2], v[3]);
+          w[1] = make_float4(v[4], v[5], v[6], v[7]);
         }
       }
       __syncthreads();
@@ -754,6 +808,93 @@ __global__ __launch_bounds__(C::NT) void igemm2_conv(GemmArgs a) {
 // WGRAD mode
 // ---------------------------------------------------------------------------
 
+#if defined(__HIP_DEVICE_COMPILE__)
+namespace {
+
+// The two A and two B values per lane of four 4-pixel MFMA steps, steps S to
+// S + 3 of the stage: 16 LDS reads and their wait in one block (the compiler
+// must not see the values before they have landed, and cannot tell these
+// reads from the LDS-DMA's targets).
+template <class C, int S>
+__device__ __forceinline__ void rd_f32x16(float (&v)[16], uint32_t a0, uint32_t a1, uint32_t b0,
+                                          uint32_t b1) {
+  constexpr int A = 4 * S * C::PA, B = C::A_BYTES + 4 * S * C::PB;
+  asm volatile(
+      "ds_read_b32 %0, %16 offset:%20\n\tds_read_b32 %1, %17 offset:%20\n\t"
+      "ds_read_b32 %2, %18 offset:%24\n\tds_read_b32 %3, %19 offset:%24\n\t"
+      "ds_read_b32 %4, %16 offset:%21\n\tds_read_b32 %5, %17 offset:%21\n\t"
+      "ds_read_b32 %6, %18 offset:%25\n\tds_read_b32 %7, %19 offset:%25\n\t"
+      "ds_read_b32 %8, %16 offset:%22\n\tds_read_b32 %9, %17 offset:%22\n\t"
+      "ds_read_b32 %10, %18 offset:%26\n\tds_read_b32 %11, %19 offset:%26\n\t"
+      "ds_read_b32 %12, %16 offset:%23\n\tds_read_b32 %13, %17 offset:%23\n\t"
+      "ds_read_b32 %14, %18 offset:%27\n\tds_read_b32 %15, %19 offset:%27"
+      : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]), "=&v"(v[4]), "=&v"(v[5]),
+        "=&v"(v[6]), "=&v"(v[7]), "=&v"(v[8]), "=&v"(v[9]), "=&v"(v[10]), "=&v"(v[11]),
+        "=&v"(v[12]), "=&v"(v[13]), "=&v"(v[14]), "=&v"(v[15])
+      : "v"(a0), "v"(a1), "v"(b0), "v"(b1), "i"(A), "i"(A + 4 * C::PA), "i"(A + 8 * C::PA),
+        "i"(A + 12 * C::PA), "i"(B), "i"(B + 4 * C::PB), "i"(B + 8 * C::PB),
+        "i"(B + 12 * C::PB));
+}
+
+// Main loop of the fp32 weight gradient.  A 16x16x4 MFMA takes one value per
+// lane: channel lane % 16 of pixel lane / 16, which the pixel-major tiles
+// hold as they are, so there is nothing to transpose.  Bound by the fp32 MFMA
+// rate (32 cycles each): a wave of 32 x 32 issues 16 MFMAs per 16 reads, and
+// the other waves of the SIMD cover the reads' wait.
+template <class C, class Issue>
+__device__ __forceinline__ void wgrad_loop_f32(uint32_t sbase, char* smem, int KT, int wm, int wn,
+                                               int lane, Issue& issue,
+                                               f32x4_t (&acc)[C::TM][C::TN]) {
+  static_assert(C::TM == 2 && C::TN == 2, "32 x 32 wave tiles");
+  const int g4 = lane >> 4, r16 = lane & 15;
+  uint32_t ra[2], rb[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int ca = wm * C::WM + i * 16 + r16, cb = wn * C::WN + i * 16 + r16;
+    ra[i] = (uint32_t)(g4 * C::PA + rot_slot(ca >> 2, g4, C::CA, C::RA_A, C::RA_B) * 16 +
+                       (ca & 3) * 4);
+    rb[i] = (uint32_t)(g4 * C::PB + rot_slot(cb >> 2, g4, C::CB, C::RB_A, C::RB_B) * 16 +
+                       (cb & 3) * 4);
+  }
+  float v[2][16];
+  // quarter q's 16 MFMAs once its values have landed, with quarter q + 1's
+  // reads (all 16 pixels further on) issued before them
+  auto quarter = [&](uint32_t sb, auto q_tag) __attribute__((always_inline)) {
+    constexpr int Q = decltype(q_tag)::value;
+    float(&x)[16] = v[Q & 1];
+    lgkm_wait<0>();
+#pragma unroll
+    for (int e = 0; e < 16; ++e) asm volatile("" : "+v"(x[e]));
+    if constexpr (Q < 3)
+      rd_f32x16<C, 4 * (Q + 1)>(v[(Q + 1) & 1], sb + ra[0], sb + ra[1], sb + rb[0], sb + rb[1]);
+    __builtin_amdgcn_sched_barrier(0);  // the reads stay above the MFMAs that cover them
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[4 * s + i], x[4 * s + 2 + j],
+                                                           acc[i][j], 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  if (KT > 0) issue(0, smem);
+  for (int kt = 0; kt < KT; ++kt) {
+    wait_vmcnt<0>();
+    __builtin_amdgcn_s_barrier();
+    const uint32_t sb = sbase + (uint32_t)((kt & 1) * C::STAGE);
+    rd_f32x16<C, 0>(v[0], sb + ra[0], sb + ra[1], sb + rb[0], sb + rb[1]);
+    if (kt + 1 < KT) issue(kt + 1, smem + ((kt + 1) & 1) * C::STAGE);
+    quarter(sb, std::integral_constant<int, 0>());
+    quarter(sb, std::integral_constant<int, 1>());
+    quarter(sb, std::integral_constant<int, 2>());
+    quarter(sb, std::integral_constant<int, 3>());
+  }
+}
+
+}  // namespace
+#endif
+
 template <class C>
 __global__ __launch_bounds__(C::NT) void igemm2_wgrad(GemmArgs a, const void* zero16) {
   // the body exists for the device pass only (the host pass emits the launch stub)
@@ -781,8 +922,8 @@ __global__ __launch_bounds__(C::NT) void igemm2_wgrad(GemmArgs a, const void* ze
   const int m0 = tmi * C::BM;
   const int n0 = (tile - tmi * tilesN) * C::BN;
 
-  const __amdgpu_buffer_rsrc_t rg = make_rsrc(a.gy.s0.ptr, P * a.gy.s0.C * 2);
-  const uint32_t gpitch = (uint32_t)(a.gy.s0.C * 2);
+  const __amdgpu_buffer_rsrc_t rg = make_rsrc(a.gy.s0.ptr, P * a.gy.s0.C * C::ESZ);
+  const uint32_t gpitch = (uint32_t)(a.gy.s0.C * C::ESZ);
 
   // Per wave load u: A loads (wl < WLA) fetch dY rows; B loads fetch the
   // shifted activation columns through per-lane addresses.  Lane slot q of
@@ -806,14 +947,14 @@ __global__ __launch_bounds__(C::NT) void igemm2_wgrad(GemmArgs a, const void* ze
       const int r = q / C::CA;
       const int lc = rot_logical(q - r * C::CA, r, C::CA, C::RA_A, C::RA_B);
       rrow[u] = r;
-      const int o = m0 + lc * 8;
-      aoff[u] = o < a.M ? (uint32_t)(o * 2) : OOB;
+      const int o = m0 + lc * C::EPC;
+      aoff[u] = o < a.M ? (uint32_t)(o * C::ESZ) : OOB;
     } else {
       const int q = (wl - C::WLA) * 64 + lane;
       const int r = q / C::CB;
       const int lc = rot_logical(q - r * C::CB, r, C::CB, C::RB_A, C::RB_B);
       rrow[u] = r;
-      const int n = n0 + lc * 8;
+      const int n = n0 + lc * C::EPC;
       if (n < a.N) {
         const int s = seg_of(a.nseg, a.seg[1].begin, a.seg[2].begin, n);
         const Seg& sg = s == 0 ? a.seg[0] : (s == 1 ? a.seg[1] : a.seg[2]);
@@ -827,8 +968,8 @@ __global__ __launch_bounds__(C::NT) void igemm2_wgrad(GemmArgs a, const void* ze
         bshift[u] = boy[u] * W + box[u];
         const bool second = c >= sg.in.c0;
         const Src& src = second ? sg.in.s1 : sg.in.s0;
-        bsrc[u] = static_cast<const char*>(src.ptr) + (second ? c - sg.in.c0 : c) * 2;
-        bpitch[u] = (uint32_t)(src.C * 2);
+        bsrc[u] = static_cast<const char*>(src.ptr) + (second ? c - sg.in.c0 : c) * C::ESZ;
+        bpitch[u] = (uint32_t)(src.C * C::ESZ);
       }
       // image coordinates of pixel pbeg + r (advanced by 64 per K-step)
       const long p = pbeg + r;
@@ -881,6 +1022,11 @@ __global__ __launch_bounds__(C::NT) void igemm2_wgrad(GemmArgs a, const void* ze
 #pragma unroll
     for (int j = 0; j < C::TN; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
+  const uint32_t sbase = lds_u32(smem);
+  const int KT = (int)((pend - pbeg + C::BK - 1) / C::BK);
+  if constexpr (C::F32) {
+    wgrad_loop_f32<C>(sbase, smem, KT, wm, wn, lane, issue, acc);
+  } else {
   // Transpose reads: lane (g16, j16) addresses pixel row
   // trow = 8 g16 + j16 / 4 (+ 32 s + 4 h) and channel 4 (j16 % 4) of a
   // fragment's 16 columns.  Row bits 0-1 and 3 are fixed per lane, so the
@@ -903,7 +1049,6 @@ __global__ __launch_bounds__(C::NT) void igemm2_wgrad(GemmArgs a, const void* ze
     rb[j] = (uint32_t)(trow * C::PB + rot_slot(col >> 3, trow, C::CB, C::RB_A, C::RB_B) * 16 +
                        (col & 7) * 2);
   }
-  const uint32_t sbase = lds_u32(smem);
 
   bf16x8_t af[2][C::TM], bfr[2][C::TN];
   auto read = [&](uint32_t sb, bf16x8_t (&fa)[C::TM], bf16x8_t (&fb)[C::TN], auto s_tag)
@@ -937,7 +1082,6 @@ __global__ __launch_bounds__(C::NT) void igemm2_wgrad(GemmArgs a, const void* ze
   // Per K-step: wait for the stage, barrier, read the first 32 pixels'
   // fragments, start the next stage's DMA, then the second half's reads
   // overlap the first half's MFMAs.
-  const int KT = (int)((pend - pbeg + C::BK - 1) / C::BK);
   if (KT > 0) issue(0, smem);
   for (int kt = 0; kt < KT; ++kt) {
     wait_vmcnt<0>();
@@ -953,6 +1097,7 @@ __global__ __launch_bounds__(C::NT) void igemm2_wgrad(GemmArgs a, const void* ze
     lgkm_wait<0>();
     mma(af[1], bfr[1]);
     __builtin_amdgcn_sched_barrier(0);
+  }
   }
   __syncthreads();
 
@@ -1078,22 +1223,54 @@ __global__ __launch_bounds__(256) void conv_splitk_finalize(GemmArgs a) {
   }
 }
 
+// Sum the split partials in split order and accumulate into the gradients
+// of each segment (rows of length end - begin: OHWI for 3x3, [O][I] for 1x1).
+// Four consecutive columns per thread (N and the segment bounds are
+// multiples of 8).
+__global__ void wgrad_finalize(GemmArgs a, int splits) {
+  const long idx = ((long)blockIdx.x * blockDim.x + threadIdx.x) * 4;
+  if (idx >= (long)a.M * a.N) return;
+  const int m = (int)(idx / a.N);
+  const int n = (int)(idx - (long)m * a.N);
+  float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int z = 0; z < splits; ++z) {
+    const float4 v = *reinterpret_cast<const float4*>(a.part + (long)z * a.M * a.N + idx);
+    s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+  }
+  const Seg sg0 = a.seg[0], sg1 = a.seg[1], sg2 = a.seg[2];
+  const int si = seg_of(a.nseg, sg1.begin, sg2.begin, n);
+  const Seg& sg = si == 0 ? sg0 : (si == 1 ? sg1 : sg2);
+  const int len = sg.end - sg.begin;
+  float* g = sg.grad + (long)m * len + (n - sg.begin);
+  g[0] += s.x; g[1] += s.y; g[2] += s.z; g[3] += s.w;
+}
+
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
 
 namespace launch2 {
-using C2_128x160 = CfgC<128, 160, 64, 80>;   // 4 waves, two blocks per CU
-using C2_128x128 = CfgC<128, 128, 64, 64>;   // 4 waves, two blocks per CU
-using C2_128x192 = CfgC<128, 192, 64, 96>;   // 4 waves, two blocks per CU
-using C2_64x128S3 = CfgC<64, 128, 32, 64, 3>;  // 4 waves, 3 stages, two blocks per CU
+using C2_128x160 = CfgC<128, 160, 64, 80, 2, 64, false, false>;   // 4 waves, two blocks per CU
+using C2_128x128 = CfgC<128, 128, 64, 64, 2, 64, false, false>;   // 4 waves, two blocks per CU
+using C2_128x192 = CfgC<128, 192, 64, 96, 2, 64, false, false>;   // 4 waves, two blocks per CU
+using C2_64x128S3 = CfgC<64, 128, 32, 64, 3, 64, false, false>;  // 4 waves, 3 stages, two blocks per CU
+// channel counts that are multiples of 32 but not of 64: 32 channels per K-step
+using C2_128x160K32 = CfgC<128, 160, 64, 80, 4, 32>;
+using C2_128x128K32 = CfgC<128, 128, 64, 64, 4, 32>;
+using C2_64x96K32 = CfgC<64, 96, 32, 48, 4, 32>;
+using C2_64x64K32 = CfgC<64, 64, 32, 32, 4, 32>;
+// fp32
+using C2_F64x64 = CfgC<64, 64, 32, 32, 3, 32, true>;
+using C2_F64x32 = CfgC<64, 32, 32, 16, 3, 32, true>;
+using C2_F32x32 = CfgC<32, 32, 16, 16, 4, 32, true>;
 using W2_320x128 = CfgW<320, 128, 80, 64>;   // 8 waves, one block per CU
 using W2_128x128 = CfgW<128, 128, 64, 64>;   // 4 waves
+using W2_F64x64 = CfgW<64, 64, 32, 32, true>;  // fp32, 4 waves, two blocks per CU
 
 template <class C>
 static hipError_t conv2_t(const GemmArgs& a_in, hipStream_t st, hipEvent_t t0, hipEvent_t t1) {
   // 32-bit pixel indices and weight offsets
-  if (a_in.g.pixels() + C::BM >= (1L << 31) || (long)a_in.N * a_in.ldb * 2 >= (1L << 31))
+  if (a_in.g.pixels() + C::BM >= (1L << 31) || (long)a_in.N * a_in.ldb * C::ESZ >= (1L << 31))
     return hipErrorInvalidValue;
   GemmArgs a = a_in;
   {
@@ -1117,7 +1294,12 @@ static hipError_t conv2_t(const GemmArgs& a_in, hipStream_t st, hipEvent_t t0, h
   const int ks = a.ksplit > 1 ? a.ksplit : 1;
   const bool fin = ks > 1 && !a.skip_finalize;  // the K-split finalize follows here
   const dim3 grid((unsigned)(tilesM * tilesN * ks)), block(C::NT);
-  auto kern = a.gnb ? igemm2_conv<C, true> : igemm2_conv<C, false>;
+  auto kern = igemm2_conv<C, false>;
+  if constexpr (C::F32) {
+    if (a.gnb) return hipErrorInvalidValue;
+  } else if (a.gnb) {
+    kern = igemm2_conv<C, true>;
+  }
   if (t0 || t1)
     hipExtLaunchKernelGGL(kern, grid, block, 0, st, t0, fin ? nullptr : t1, 0, a);
   else
@@ -1175,24 +1357,35 @@ static TileInfo info2() {
 }  // namespace launch2
 using namespace launch2;
 
+// f(tag) with the configuration of conv tile t
+template <class F>
+static auto with_conv(int t, F f) {
+  switch (t) {
+    case TILE2_C128x160: return f(C2_128x160());
+    case TILE2_C128x192: return f(C2_128x192());
+    case TILE2_C64x128S3: return f(C2_64x128S3());
+    case TILE2_C128x160K32: return f(C2_128x160K32());
+    case TILE2_C128x128K32: return f(C2_128x128K32());
+    case TILE2_C64x96K32: return f(C2_64x96K32());
+    case TILE2_C64x64K32: return f(C2_64x64K32());
+    case TILE2_F64x64: return f(C2_F64x64());
+    case TILE2_F64x32: return f(C2_F64x32());
+    case TILE2_F32x32: return f(C2_F32x32());
+    default: return f(C2_128x128());
+  }
+}
+
 TileInfo tile2_info(int t) {
   switch (t) {
-    case TILE2_C128x160: return info2<C2_128x160>();
-    case TILE2_C128x128: return info2<C2_128x128>();
-    case TILE2_C128x192: return info2<C2_128x192>();
-    case TILE2_C64x128S3: return info2<C2_64x128S3>();
     case TILE2_W320x128: return info2<W2_320x128>();
-    default: return info2<W2_128x128>();
+    case TILE2_W128x128: return info2<W2_128x128>();
+    case TILE2_WF64x64: return info2<W2_F64x64>();
+    default: return with_conv(t, [](auto c) { return info2<decltype(c)>(); });
   }
 }
 
 hipError_t launch_conv2(const GemmArgs& a, int t, hipStream_t st, hipEvent_t t0, hipEvent_t t1) {
-  switch (t) {
-    case TILE2_C128x160: return conv2_t<C2_128x160>(a, st, t0, t1);
-    case TILE2_C128x192: return conv2_t<C2_128x192>(a, st, t0, t1);
-    case TILE2_C64x128S3: return conv2_t<C2_64x128S3>(a, st, t0, t1);
-    default: return conv2_t<C2_128x128>(a, st, t0, t1);
-  }
+  return with_conv(t, [&](auto c) { return conv2_t<decltype(c)>(a, st, t0, t1); });
 }
 
 hipError_t launch_wgrad2(const GemmArgs& a, int t, int splits, const void* zero16,
@@ -1200,10 +1393,14 @@ hipError_t launch_wgrad2(const GemmArgs& a, int t, int splits, const void* zero1
   hipError_t e;
   switch (t) {
     case TILE2_W320x128: e = wgrad2_t<W2_320x128>(a, splits, zero16, st); break;
+    case TILE2_WF64x64: e = wgrad2_t<W2_F64x64>(a, splits, zero16, st); break;
     default: e = wgrad2_t<W2_128x128>(a, splits, zero16, st); break;
   }
   if (e != hipSuccess || wgrad_direct(a, splits)) return e;  // added in the epilogue
-  return launch_wgrad_finalize(a, splits, st);
+  const long total = (long)a.M * a.N / 4;
+  hipLaunchKernelGGL(wgrad_finalize, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, a,
+                     splits);
+  return hipGetLastError();
 }
 
 }  // namespace pulse

@@ -38,7 +38,7 @@ struct GemmArgs {
   void* out2;          // optional second copy of out
   int out_dtype;
   int ldo;
-  int ksplit;          // K splits (conv mode, LDS-DMA path): > 1 writes fp32
+  int ksplit;          // K splits (conv mode): > 1 writes fp32
   int ksteps;          // partials to part and a finalize applies the epilogue;
                        // ksteps = K-steps per split
   // WGRAD mode
@@ -48,8 +48,8 @@ struct GemmArgs {
   int wdirect;         // set by the wgrad launcher: one pixel split, so the
                        // epilogue adds its tile into the segment gradients
                        // (one writer per element) and no finalize runs
-  // CONV mode of the LDS-DMA kernels without a K split, when H*W % BM == 0:
-  // per-channel sum and sum of squares of the output as stored (bf16), one
+  // CONV mode without a K split, when H*W % BM == 0:
+  // per-channel sum and sum of squares of the output as stored, one
   // row per (image, M-tile): [B][H*W / BM][2][N]; null: not computed
   float* stats;
   // Same conditions: the GroupNorm+SiLU backward sums of the output taken as
@@ -83,36 +83,34 @@ inline uint32_t rcp_u32(uint64_t d, uint64_t nmax) {
   return (uint32_t)(0xffffffffull / d + 1);
 }
 
-// implicit GEMM, register-staged (igemm.hip): the fp32 stage and bf16
-// channel counts that are multiples of 32 but not of 64
-enum Tile : int {
-  TILE_128x128_K32 = 0,  // bf16, 32 channels per K-step
-  TILE_64x64_F32 = 1,    // fp32, 32 channels per K-step
-  TILE_COUNT = 2
-};
-struct TileInfo {
-  int bm, bn, bk;
-  int per_cu;  // blocks resident per CU (LDS-limited), 0 when not known
-};
-TileInfo tile_info(int tile);
-hipError_t launch_conv(const GemmArgs& a, int tile, hipStream_t st);
-hipError_t launch_wgrad(const GemmArgs& a, int tile, int splits, hipStream_t st);
-hipError_t launch_wgrad_finalize(const GemmArgs& a, int splits, hipStream_t st);
-
-// second generation (igemm2.hip): LDS-DMA operand loads, bf16 with 64
-// channels per K-step.  zero16: 16 zero bytes of device memory.
+// Implicit GEMM (igemm2.hip): LDS-DMA operand loads.  Which tile serves which
+// stage: bf16 with every channel count a multiple of 64 (64 channels per
+// K-step), bf16 with multiples of 32 (32 per K-step), and fp32.
 enum Tile2 : int {
   TILE2_C128x160 = 0,   // 4 waves of 64 x 80, two blocks per CU
   TILE2_C128x128 = 1,   // 4 waves of 64 x 64, two blocks per CU
   TILE2_C128x192 = 2,   // 4 waves of 64 x 96, two blocks per CU
   TILE2_C64x128S3 = 3,  // 4 waves of 32 x 64, three LDS stages, two blocks per CU
-  TILE2_CONV_LAST = 3,
+  TILE2_CONV_LAST = 3,  // of the 64-channel tiles
+  TILE2_C128x160K32 = 8,
+  TILE2_C128x128K32 = 9,
+  TILE2_C64x96K32 = 10,
+  TILE2_C64x64K32 = 11,
+  TILE2_F64x64 = 12,    // fp32, 4 waves of 32 x 32
+  TILE2_F64x32 = 13,    // fp32, 4 waves of 32 x 16
+  TILE2_F32x32 = 14,    // fp32, 4 waves of 16 x 16
   TILE2_W320x128 = 20,  // 8 waves of 80 x 64, one block per CU
   TILE2_W128x128 = 21,  // 4 waves of 64 x 64
   TILE2_WGRAD_FIRST = 20,
-  TILE2_WGRAD_LAST = 21
+  TILE2_WGRAD_LAST = 21,
+  TILE2_WF64x64 = 22    // fp32, 4 waves of 32 x 32
+};
+struct TileInfo {
+  int bm, bn, bk;
+  int per_cu;  // blocks resident per CU (LDS-limited)
 };
 TileInfo tile2_info(int tile);
+// zero16: 16 zero bytes of device memory.
 // t0 / t1 (may be null): events recorded by the GEMM kernel's own start and
 // by the completion of the launch's last kernel (the GEMM or its K-split
 // finalize), which time the launch without marker packets around it.
@@ -138,7 +136,7 @@ hipError_t launch_gn_stats_partial(const VIn& x, const Geo& g, RedGrid rg, float
                                    hipStream_t st, void* copy = nullptr);
 // mean/rstd [B][G] and the folded affine scale/shift [B][C].
 // K-split conv finalize that also reduces the output: out = sum_z part[z]
-// (fixed order) + bias + rowvec + residual (bf16), and the per-channel sum
+// (fixed order) + bias + rowvec + residual, and the per-channel sum
 // and sum of squares of the stored output per (image, chunk of the reduction
 // grid rg over N channels) row of a.stats.
 hipError_t launch_splitk_finalize_stats(const GemmArgs& a, RedGrid rg, hipStream_t st,

@@ -679,9 +679,10 @@ __global__ __launch_bounds__(256) void k_chan_sum_partial(VIn v, Geo g, RedGrid 
 // the GroupNorm kernels: thread (channel vector, pixel lane) sums the fp32
 // partials of its 8 channels in split order (two pixels per step, their
 // loads in flight together), adds bias, the timestep row and the residual,
-// stores bf16 and accumulates the sum and sum of squares of the stored
+// stores them (DT) and accumulates the sum and sum of squares of the stored
 // values; the lanes meet in LDS (one row per chunk).  (The GroupNorm-
 // backward sums measured slower here than in their own pass.)
+template <int DT>
 __global__ __launch_bounds__(256) void k_splitk_finalize_stats(GemmArgs a, RedGrid rg) {
   __shared__ float sm[256 * 16];
   const Geo g = a.g;
@@ -729,11 +730,11 @@ __global__ __launch_bounds__(256) void k_splitk_finalize_stats(GemmArgs a, RedGr
 #pragma unroll
           for (int q = 0; q < 8; ++q) v[q] += t[q];
         }
-        st8(a.out, DT_BF16, a.ldo, px[u], r.c, v);
-        if (a.out2) st8(a.out2, DT_BF16, a.ldo, px[u], r.c, v);
+        st8(a.out, DT, a.ldo, px[u], r.c, v);
+        if (a.out2) st8(a.out2, DT, a.ldo, px[u], r.c, v);
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
-          const float b = bf2f(f2bf(v[q]));  // as stored
+          const float b = DT == DT_BF16 ? bf2f(f2bf(v[q])) : v[q];  // as stored
           acc[q] += b;
           acc[8 + q] += b * b;
         }
@@ -793,15 +794,16 @@ hipError_t launch_gn_stats_partial(const VIn& x, const Geo& g, RedGrid rg, float
 
 hipError_t launch_splitk_finalize_stats(const GemmArgs& a, RedGrid rg, hipStream_t st,
                                         hipEvent_t done) {
-  if (a.ksplit < 2 || !a.part || !a.stats || a.gnb || a.out_dtype != DT_BF16 || a.ldo != a.N ||
-      a.N % 8 != 0 || (a.resid.s0.ptr && (a.resid.s0.dtype != DT_BF16 || a.resid.add)))
+  if (a.ksplit < 2 || !a.part || !a.stats || a.gnb || a.ldo != a.N || a.N % 8 != 0 ||
+      (a.resid.s0.ptr && (a.resid.s0.dtype != a.out_dtype || a.resid.add)))
     return hipErrorInvalidValue;
+  auto kern =
+      a.out_dtype == DT_BF16 ? k_splitk_finalize_stats<DT_BF16> : k_splitk_finalize_stats<DT_F32>;
   if (done)
-    hipExtLaunchKernelGGL(k_splitk_finalize_stats, red_dims(a.g, rg, a.N), red_block(rg), 0, st,
+    hipExtLaunchKernelGGL(kern, red_dims(a.g, rg, a.N), red_block(rg), 0, st,
                           nullptr, done, 0, a, rg);
   else
-    hipLaunchKernelGGL(k_splitk_finalize_stats, red_dims(a.g, rg, a.N), red_block(rg), 0, st, a,
-                       rg);
+    hipLaunchKernelGGL(kern, red_dims(a.g, rg, a.N), red_block(rg), 0, st, a, rg);
   return hipGetLastError();
 }
 

@@ -188,6 +188,8 @@ struct pulse_stage {
   char* fwd_base = nullptr;
   size_t f_red = 0, f_e = 0, f_kpart = 0, f_kcap = 0;
   size_t fs_red = 0, fs_e = 0, fs_kpart = 0, fs_kcap = 0, fs_bytes = 0;  // compact layout
+  long fwd_part_cap = -1;  // forward partials (floats) that keep that layout in the static
+                           // array; -1: it does not fit even without them
   float* fwd(size_t off) const { return reinterpret_cast<float*>(fwd_base + off); }
   void use_workspace_scratch() {
     fwd_base = ws + off_scratch;
@@ -254,41 +256,74 @@ void layout_gn(const pulse_stage* s, GnSave& g, size_t& off, int C) {
   off += align256((size_t)s->geo.B * C * 4);
 }
 
-// Tile shape of a conv-mode GEMM with N output columns (a Tile2 value on
-// the LDS-DMA path, a Tile value otherwise).
+long conv_tiles(const pulse_stage* s, int tile, int N) {
+  const TileInfo ti = tile2_info(tile);
+  return ((s->P + ti.bm - 1) / ti.bm) * ((N + ti.bn - 1) / ti.bn);
+}
+
+// Tile shape of a conv-mode GEMM with N output columns.
 int conv_tile(const pulse_stage* s, int N) {
-  if (s->dtype == DT_F32) return TILE_64x64_F32;
-  if (!s->k64) return TILE_128x128_K32;
+  if (s->dtype == DT_F32) {
+    // fp32 MFMAs bound these: the tile whose rounds of one block per CU cost
+    // least, a K-step of bm x bn taking about 0.19 us + 0.15 us per 1024
+    // outputs (4 x 24 x 40 pixels: 128 -> 128 channels 21 us with 64 x 32
+    // against 30 with 64 x 64; 128 -> 256 30 us with 64 x 64 against 33 with
+    // 32 x 32; 1 x 32 x 32: 15 us with 32 x 32 against 29 with 64 x 64)
+    int best = TILE2_F64x64;
+    double least = 1e30;
+    for (int t : {TILE2_F64x64, TILE2_F64x32, TILE2_F32x32}) {
+      const TileInfo ti = tile2_info(t);
+      const double cost = (double)((conv_tiles(s, t, N) + 255) / 256) *
+                          (0.19 + 0.15 * ti.bm * ti.bn / 1024.0);
+      if (cost < least) {
+        least = cost;
+        best = t;
+      }
+    }
+    return best;
+  }
+  if (!s->k64) {
+    // 128-row tiles where they fill the GPU (with a K split in two from 200
+    // blocks on) and waste no more than a fifth of their columns; 64 x 96
+    // below (3 x 27 x 45 pixels, 288 -> 288: 24 us against 27 for 128 x 128
+    // and 27 for 128 x 160; 8 x 32 x 32, 480 -> 480: 70 against 55 and 60)
+    const int big = N % 160 == 0 ? TILE2_C128x160K32 : TILE2_C128x128K32;
+    const int bn = tile2_info(big).bn;
+    const bool wasteful = 5L * ((N + bn - 1) / bn) * bn > 6L * ((N + 95) / 96) * 96;
+    return conv_tiles(s, big, N) >= 200 && !wasteful ? big : TILE2_C64x96K32;
+  }
   if (s->conv_tile_force >= 0) return s->conv_tile_force;
   return N % 160 == 0 ? TILE2_C128x160 : TILE2_C128x128;
 }
 
 // Tile shape of a weight-gradient GEMM (M output channels, N columns).
 int wgrad_tile(const pulse_stage* s, int M, int N) {
-  if (s->dtype == DT_F32) return TILE_64x64_F32;
-  if (!s->k64) return TILE_128x128_K32;
+  if (s->dtype == DT_F32) return TILE2_WF64x64;
   if (s->wgrad_tile_force >= 0) return s->wgrad_tile_force;
   (void)N;
   return M % 320 == 0 ? TILE2_W320x128 : TILE2_W128x128;
 }
 
-// bf16 with every channel count a multiple of 64: the LDS-DMA kernels
-bool uses_v2(const pulse_stage* s) { return s->dtype == DT_BF16 && s->k64; }
-
-TileInfo info_of(const pulse_stage* s, int tile) {
-  return uses_v2(s) ? tile2_info(tile) : tile_info(tile);
-}
-
-// K splits of a conv-mode GEMM on the LDS-DMA path: enough blocks for two
-// per CU (the tile's occupancy), each split keeping at least 4 K-steps.
-int conv_ksplit(const pulse_stage* s, int tile, int N, int K) {
-  if (!uses_v2(s)) return 1;
-  const TileInfo ti = info_of(s, tile);
-  const long tiles = ((s->P + ti.bm - 1) / ti.bm) * ((N + ti.bn - 1) / ti.bn);
-  const long want = 512;
-  if (tiles >= want) return 1;
-  long ks = (want + tiles - 1) / tiles;
-  ks = std::min(ks, std::max(1L, (long)(K / ti.bk) / 4));
+// K splits of a conv-mode GEMM: enough blocks for two per CU (the tile's
+// occupancy), each split keeping at least 4 K-steps.  The fp32 and the
+// 32-channel tiles pay about 7 us for the partials' finalize and so split
+// only long K: fp32 from 128 blocks down to fill the GPU once, 9 or more
+// K-steps per split (1 x 32 x 32, 128 -> 128: 12 us in two splits against
+// 15); 32-channel tiles to two blocks per CU, 18 or more K-steps per split
+// (3 x 27 x 45: 288 -> 96 16 us in four against 28 in one, 96 -> 288, 27
+// K-steps, 13 us in one against 17 in two).  `fwd` (a forward conv): the
+// partials of a stage whose forward scratch without them fits the static
+// scratch array leave it fitting.
+int conv_ksplit(const pulse_stage* s, int tile, int N, int K, bool fwd) {
+  const TileInfo ti = tile2_info(tile);
+  const long tiles = conv_tiles(s, tile, N);
+  const long kt = K / ti.bk;
+  const bool few = s->dtype == DT_F32 || !s->k64;
+  const long want = s->dtype == DT_F32 ? 256 : 512;
+  if (tiles >= want || (s->dtype == DT_F32 && tiles > 128)) return 1;
+  long ks = few ? want / tiles : (want + tiles - 1) / tiles;
+  ks = std::min(ks, std::max(1L, kt / (s->dtype == DT_F32 ? 9 : s->k64 ? 4 : 18)));
+  if (fwd && few && s->fwd_part_cap >= 0) ks = std::min(ks, std::max(1L, s->fwd_part_cap / (s->P * N)));
   return (int)std::min(ks, (long)s->conv_ksplit_cap);
 }
 
@@ -299,21 +334,22 @@ int conv_ksplit(const pulse_stage* s, int tile, int N, int K) {
 // the fp32 gradient.  The split count minimises
 //   rounds(s) * T_tile / s + bytes(s) * M * N / HBM
 // where T_tile is one tile's whole-K time at a nominal per-CU rate and
-// bytes(s) = 8 s + 8; on the LDS-DMA path one split adds its tile into the
-// gradient in the GEMM epilogue (no partial, no finalize): bytes(1) = 8.
+// bytes(s) = 8 s + 8; one split adds its tile into the gradient in the GEMM
+// epilogue (no partial, no finalize): bytes(1) = 8.
 int pick_splits(const pulse_stage* s, int tile, int M, int N, int& kchunk) {
-  const TileInfo ti = info_of(s, tile);
+  const TileInfo ti = tile2_info(tile);
   const long tiles = (long)((M + ti.bm - 1) / ti.bm) * ((N + ti.bn - 1) / ti.bn);
-  const long per_cu = ti.per_cu > 0 ? std::min(ti.per_cu, 2) : (ti.bm * ti.bn <= 128 * 128 ? 2 : 1);
-  const long slots = 256L * per_cu;  // resident blocks
-  const double t_tile = 2.0 * ti.bm * ti.bn * (double)s->P / 3.0e12;  // s, per CU
+  // resident blocks (fp32: one fills a CU's matrix cores)
+  const long slots = 256L * (s->dtype == DT_F32 ? 1 : std::min(ti.per_cu, 2));
+  // s per CU (fp32: the nominal matrix rate is a sixteenth)
+  const double t_tile = 2.0 * ti.bm * ti.bn * (double)s->P / (s->dtype == DT_F32 ? 3.0e11 : 3.0e12);
   const double t_elem = (double)M * N / 4.0e12;                       // s per byte per element
   const long maxs = std::max(1L, (long)(s->P / (4 * ti.bk)));          // >= 4 K-steps each
   long best = 1;
   double best_t = 1e30;
   for (long sp = 1; sp <= std::min(maxs, 256L); ++sp) {
     const long rounds = (tiles * sp + slots - 1) / slots;
-    const double bytes = sp == 1 && uses_v2(s) ? 8.0 : 8.0 * sp + 8.0;
+    const double bytes = sp == 1 ? 8.0 : 8.0 * sp + 8.0;
     const double t = rounds * t_tile / sp + bytes * t_elem;
     if (t < best_t * 0.999) {
       best_t = t;
@@ -461,7 +497,7 @@ pulse_status build_layout(pulse_stage* s) {
         RedGrid rg = red_grid(s->geo, c);
         red = std::max(red, (size_t)s->geo.B * rg.chunks * 2 * c);
         // conv-mode K-split partials (an upper bound over the K of each launch)
-        const int ks = conv_ksplit(s, conv_tile(s, c), c, 1 << 30);
+        const int ks = conv_ksplit(s, conv_tile(s, c), c, 1 << 30, false);
         if (ks > 1) kpart = std::max(kpart, (size_t)ks * s->P * c);
       }
     }
@@ -484,21 +520,25 @@ pulse_status build_layout(pulse_stage* s) {
   s->s_e = sc; sc += align256(nblk * s->geo.B * cmax * 4);
   s->s_zero = sc; sc += 256;  // zero bytes read in place of out-of-image taps
   s->ws_bytes = s->off_scratch + sc;
-  // the forward's scratch alone, packed (pulse_stage_forward_static), with
-  // the K-split partials of the forward convs only, at their own K
+  // the forward's scratch without conv partials, packed
+  // (pulse_stage_forward_static)
+  size_t fs = 0;
+  s->fs_red = fs; fs += align256(red * 4);
+  s->fs_e = fs; fs += align256(nblk * s->geo.B * cmax * 4);
+  s->fs_kpart = fs;
+  s->fwd_part_cap = fs <= PULSE_FWD_STATIC_SCRATCH_BYTES
+                        ? (long)(PULSE_FWD_STATIC_SCRATCH_BYTES - fs) / 4 : -1;
+  // and with the K-split partials of the forward convs only, at their own K
   size_t fkpart = 0;
   for (auto* v : {&s->eb, &s->db})
     for (auto& b : *v) {
       const int k2 = 9 * b.cout + (b.conv_sc ? b.cin : 0);
       for (int K : {9 * b.cin, k2}) {
-        const int ks = conv_ksplit(s, conv_tile(s, b.cout), b.cout, K);
+        const int ks = conv_ksplit(s, conv_tile(s, b.cout), b.cout, K, true);
         if (ks > 1) fkpart = std::max(fkpart, (size_t)ks * s->P * b.cout);
       }
     }
-  size_t fs = 0;
-  s->fs_red = fs; fs += align256(red * 4);
-  s->fs_e = fs; fs += align256(nblk * s->geo.B * cmax * 4);
-  s->fs_kpart = fs; fs += align256(fkpart * 4);
+  fs += align256(fkpart * 4);
   s->fs_kcap = fkpart;
   s->fs_bytes = fs;
   return PULSE_OK;
@@ -697,11 +737,12 @@ double conv_bytes(const pulse_stage* s, const GemmArgs& a) {
   return b;
 }
 
-pulse_status run_conv(pulse_stage* s, GemmArgs& a, hipStream_t st, int* stats_chunks = nullptr) {
+pulse_status run_conv(pulse_stage* s, GemmArgs& a, hipStream_t st, bool fwd,
+                      int* stats_chunks) {
   if (stats_chunks) *stats_chunks = 0;
   const int tile = conv_tile(s, a.N);
-  const int ks = conv_ksplit(s, tile, a.N, a.K);
-  const int kt = a.K / info_of(s, tile).bk;
+  const int ks = conv_ksplit(s, tile, a.N, a.K, fwd);
+  const int kt = a.K / tile2_info(tile).bk;
   a.ksplit = ks;
   a.ksteps = (kt + ks - 1) / ks;
   if (ks > 1) {
@@ -710,31 +751,28 @@ pulse_status run_conv(pulse_stage* s, GemmArgs& a, hipStream_t st, int* stats_ch
       return fail(PULSE_E_SHAPE, "internal: conv partial buffer too small");
     a.part = s->fwd(s->f_kpart);
   }
-  // timed launches: the implicit-GEMM kernels record the events themselves
-  // at their start and completion; the register-staged path between markers
+  // timed launches: the kernels record the events at their start and completion
   hipEvent_t e0 = nullptr, e1 = nullptr;
   if (s->timing) {
     e0 = next_event(s);
     e1 = next_event(s);
   }
   const bool timed = e0 && e1;
-  const bool on_kernel = timed && uses_v2(s);
-  if (timed && !on_kernel) HIPCHK(hipEventRecord(e0, st));
   // Output statistics, or the GroupNorm-backward sums, from the conv: its
   // epilogue without a K split (whole tiles per image); with a K split the
   // statistics (not the backward sums, which measured slower there) from
   // the finalize on the reduction grid; with room in the reduction buffer.
   // Otherwise the caller's GroupNorm computes them itself (stats_chunks
   // stays 0).
-  const bool want = (a.stats || a.gnb) && stats_chunks && uses_v2(s) &&
-                    !(a.gnb && s->no_gnb);
+  const bool want = (a.stats || a.gnb) && stats_chunks &&
+                    !(a.gnb && (s->no_gnb || s->dtype == DT_F32));
   bool red_fin = false;
   if (want && a.ksplit == 1) {
-    const int bm = info_of(s, tile).bm;
+    const int bm = tile2_info(tile).bm;
     const long rows = s->geo.hw() % bm == 0 ? (long)s->geo.B * (s->geo.hw() / bm) : 0;
     if (rows > 0 && (size_t)rows * 2 * a.N <= s->red_cap)
       *stats_chunks = s->geo.hw() / bm;
-  } else if (want && a.stats && a.N % 8 == 0 && a.ldo == a.N && a.out_dtype == DT_BF16) {
+  } else if (want && a.stats && a.N % 8 == 0 && a.ldo == a.N && a.out_dtype == s->dtype) {
     const RedGrid rg = red_grid(s->geo, a.N);
     if ((size_t)s->geo.B * rg.chunks * 2 * a.N <= s->red_cap) {
       *stats_chunks = rg.chunks;
@@ -750,18 +788,13 @@ pulse_status run_conv(pulse_stage* s, GemmArgs& a, hipStream_t st, int* stats_ch
     k.stats = nullptr;
     k.gnb = nullptr;
     k.skip_finalize = 1;
-    HIPCHK(launch_conv2(k, tile, st, on_kernel ? e0 : nullptr, nullptr));
-    HIPCHK(launch_splitk_finalize_stats(a, red_grid(s->geo, a.N), st,
-                                        on_kernel ? e1 : nullptr));
-  } else if (uses_v2(s)) {
-    HIPCHK(launch_conv2(a, tile, st, on_kernel ? e0 : nullptr, on_kernel ? e1 : nullptr));
+    HIPCHK(launch_conv2(k, tile, st, timed ? e0 : nullptr, nullptr));
+    HIPCHK(launch_splitk_finalize_stats(a, red_grid(s->geo, a.N), st, timed ? e1 : nullptr));
   } else {
-    HIPCHK(launch_conv(a, tile, st));
+    HIPCHK(launch_conv2(a, tile, st, timed ? e0 : nullptr, timed ? e1 : nullptr));
   }
-  if (timed) {
-    if (!on_kernel) HIPCHK(hipEventRecord(e1, st));
+  if (timed)
     s->timed.push_back(TimedLaunch{e0, e1, 2.0 * (double)a.M * a.N * a.K, conv_bytes(s, a)});
-  }
   return PULSE_OK;
 }
 
@@ -812,7 +845,7 @@ pulse_status conv_fwd(pulse_stage* s, int N, std::initializer_list<Seg> segs, co
                       int ldb, const float* bias, const float* rowvec, const VIn& resid,
                       void* out, void* out2, int out_dtype, hipStream_t st,
                       float* stats = nullptr, int* stats_chunks = nullptr,
-                      const GnbReq* gnb = nullptr) {
+                      const GnbReq* gnb = nullptr, bool fwd = false) {
   GemmArgs a = gemm_base(s);
   a.M = (int)s->P;
   a.N = N;
@@ -841,7 +874,7 @@ pulse_status conv_fwd(pulse_stage* s, int N, std::initializer_list<Seg> segs, co
     a.gnb_rstd = gnb->rstd;
     a.gnb_G = s->G;
   }
-  return run_conv(s, a, st, stats_chunks);
+  return run_conv(s, a, st, fwd, stats_chunks);
 }
 
 pulse_status wgrad(pulse_stage* s, int M, std::initializer_list<Seg> segs, const VIn& gy,
@@ -863,10 +896,7 @@ pulse_status wgrad(pulse_stage* s, int M, std::initializer_list<Seg> segs, const
     return fail(PULSE_E_SHAPE, "internal: wgrad partial buffer too small");
   a.kchunk = w.kchunk;
   a.part = s->sf(s->s_part);
-  if (uses_v2(s))
-    HIPCHK(launch_wgrad2(a, tile, splits, s->scratch(s->s_zero), st));
-  else
-    HIPCHK(launch_wgrad(a, tile, splits, st));
+  HIPCHK(launch_wgrad2(a, tile, splits, s->scratch(s->s_zero), st));
   return PULSE_OK;
 }
 
@@ -978,7 +1008,8 @@ pulse_status block_forward(pulse_stage* s, int r, const Block& b, const VIn& xin
   void* h1 = row + b.h1;
   int h1_chunks = 0;  // GN2 statistics of h1 from conv1's epilogue, when it can
   if ((ps = conv_fwd(s, b.cout, {seg3(0, b.cin, a1)}, s->ws + b.wf1, 9 * b.cin, nullptr, e,
-                     vnone(), h1, nullptr, dt, st, s->fwd(s->f_red), &h1_chunks)) != PULSE_OK)
+                     vnone(), h1, nullptr, dt, st, s->fwd(s->f_red), &h1_chunks, nullptr,
+                     true)) != PULSE_OK)
     return ps;
   // a2 = SiLU(GN2(h1))
   const VIn h1v = vin1(h1, dt, b.cout);
@@ -992,9 +1023,9 @@ pulse_status block_forward(pulse_stage* s, int r, const Block& b, const VIn& xin
   if (b.conv_sc)
     return conv_fwd(s, b.cout, {seg3(0, b.cout, a2v), seg1(9 * b.cout, b.cin, xin)},
                     s->ws + b.wf2, b.ldb2, bias2, nullptr, vnone(), out, out2, dt, st, ostats,
-                    out_chunks);
+                    out_chunks, nullptr, true);
   return conv_fwd(s, b.cout, {seg3(0, b.cout, a2v)}, s->ws + b.wf2, b.ldb2, bias2, nullptr, xin,
-                  out, out2, dt, st, ostats, out_chunks);
+                  out, out2, dt, st, ostats, out_chunks, nullptr, true);
 }
 
 // One ResBlock backward.  dout: gradient w.r.t. the block output.  o: where
@@ -1119,7 +1150,7 @@ pulse_status block_backward(pulse_stage* s, int r, const Block& b, const VIn& xi
                     vnone(), dxs, nullptr, dt, st);
   };
   const bool sc_first =
-      b.conv_sc && conv_ksplit(s, conv_tile(s, b.cout), b.cout, 9 * b.cout) == 1;
+      b.conv_sc && conv_ksplit(s, conv_tile(s, b.cout), b.cout, 9 * b.cout, false) == 1;
   if (sc_first) {
     if ((ps = shortcut_dgrad()) != PULSE_OK) return ps;
     s->fork_attached = false;  // the fork below orders the side stream after it

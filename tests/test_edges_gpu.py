@@ -33,3 +33,21 @@ def test_refresh_job_tables(dtype, c):
     """5 + 5 blocks make 36 weight-copy jobs (two tables of 32), with rows
     and columns that are not multiples of the 64 x 64 tile."""
     _parity(_pair(1, 5, 3, c, 8, 64, dtype, 5), 21, f"refresh-{dtype}")
+
+
+# fp32 tiles (64 x 64, 64 x 32, 32 x 32, a K split) and 32-channel bf16 tiles
+# (64 x 96 with and without a K split, 128 x 128 and 128 x 160, in one and
+# two K splits): remainders in rows and columns, images smaller than a tile
+CONV_EDGES = [
+    (configs.F32, 1, 3, 5, 96, 32, 1), (configs.F32, 2, 33, 31, 64, 16, 1),
+    (configs.F32, 4, 48, 48, 160, 32, 1), (configs.F32, 1, 16, 16, 224, 32, 1),
+    (configs.BF16, 1, 7, 3, 32, 8, 1), (configs.BF16, 3, 27, 45, 96, 32, 1),
+    (configs.BF16, 2, 13, 11, 288, 32, 1), (configs.BF16, 7, 61, 59, 160, 32, 1),
+    (configs.BF16, 9, 57, 64, 224, 32, 1), (configs.BF16, 2, 16, 16, 352, 32, 1),
+]
+
+
+@pytest.mark.parametrize("dtype,batch,h,w,c,groups,n", CONV_EDGES,
+                         ids=[f"{d}-{b}x{h}x{w}x{c}" for d, b, h, w, c, _, _ in CONV_EDGES])
+def test_conv_tiles(dtype, batch, h, w, c, groups, n):
+    _parity(_pair(batch, h, w, c, groups, 64, dtype, n), 22, f"{dtype} {batch}x{h}x{w}x{c}")
