@@ -74,14 +74,15 @@ __device__ __forceinline__ void wait_stages(int after) {
 // fp32 values and a fragment is 16 bytes per lane either way: 8 bf16 k
 // values of one MFMA, or one fp32 k value of each of four.
 template <int BM_, int BN_, int WM_, int WN_, int STAGES_ = 2, int BK_ = 64, bool F32_ = false,
-          bool RDF_ = true>
+          int KG_ = 1>
 struct CfgC {
-  static constexpr bool RDF = RDF_;
   static constexpr bool F32 = F32_;
   static constexpr int ESZ = F32 ? 4 : 2;     // bytes per element
   static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, BK = BK_, STAGES = STAGES_;
+  // NW waves per K group, KG groups per block
+  static constexpr int KG = KG_;
   static constexpr int WAVES_M = BM / WM, WAVES_N = BN / WN, NW = WAVES_M * WAVES_N;
-  static constexpr int NT = NW * 64;
+  static constexpr int NT = NW * 64 * KG;
   static constexpr int TM = WM / 16, TN = WN / 16;
   static constexpr int RB = BK * ESZ;         // row bytes
   static constexpr int CPR = RB / 16;         // 16-byte chunks per row
@@ -95,13 +96,14 @@ struct CfgC {
   static constexpr int NU_LO = WL / NW;           // loads of waves >= REM
   static constexpr int UA = WLA / NW;  // loads u < UA fill A, the rest fill B
   static constexpr int LDC = BN + 4;
-  static constexpr int LDS_BYTES = STAGES * STAGE;
+  static constexpr int LDS_BYTES = KG * STAGES * STAGE;
   static_assert(RB == 64 || RB == 128, "K-step");
   static_assert(STAGES >= 2 && (STAGES - 2) * NU < 64, "vmcnt");
   static_assert(16 * LDC * 4 <= STAGES * STAGE, "epilogue slice must fit the stages");
   static_assert(F32 || (2 * 16 * LDC + 4 * BN) * 4 <= STAGES * STAGE,
                 "GroupNorm-backward slices and constants must fit the stages");
-  static_assert(STAGES * STAGE <= 160 * 1024, "LDS");
+  static_assert(LDS_BYTES <= 160 * 1024 && NT <= 1024, "LDS, threads");
+  static_assert((KG - 1) * TM * TN * NW * 1024 <= LDS_BYTES, "the groups' sums meet in the stages");
   static_assert(A_BYTES % 1024 == 0 && B_BYTES % 1024 == 0, "whole wave loads");
   static_assert(WLA % NW == 0, "A wave loads must split evenly over the waves");
   static_assert(A_BYTES + (TN - 1) * 16 * RB < 65536, "fragment offsets are 16-bit immediates");
@@ -352,10 +354,14 @@ template <class C, bool GNB = false>
 __global__ __launch_bounds__(C::NT) void igemm2_conv(GemmArgs a) {
   // the body exists for the device pass only (the host pass emits the launch stub)
 #if defined(__HIP_DEVICE_COMPILE__)
-  __shared__ __attribute__((aligned(1024))) char smem[C::STAGES * C::STAGE];
+  __shared__ __attribute__((aligned(1024))) char smem[C::LDS_BYTES];
   const int tid = threadIdx.x;
   const int lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: scalar registers
+  // uniform: scalar registers; kg: the wave's K group, with its own stages
+  const int wave_b = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kg = C::KG > 1 ? wave_b / C::NW : 0;
+  const int wave = wave_b - kg * C::NW;
+  char* const gsmem = smem + kg * (C::STAGES * C::STAGE);
   const int wm = wave % C::WAVES_M;
   const int wn = wave / C::WAVES_M;
 
@@ -389,8 +395,11 @@ __global__ __launch_bounds__(C::NT) void igemm2_conv(GemmArgs a) {
   const long m0 = (long)tm * C::BM;
   const int n0 = tn * C::BN;
   const int KT_ALL = a.K / C::BK;
-  const int kt0 = z * a.ksteps;
-  const int KT = min(KT_ALL, kt0 + a.ksteps) - kt0;  // K-steps of this block
+  const int ktb = z * a.ksteps;
+  const int KTB = min(KT_ALL, ktb + a.ksteps) - ktb;  // K-steps of this block
+  const int KTL = (KTB + C::KG - 1) / C::KG;          // of its longest K group
+  const int kt0 = ktb + kg * KTL;
+  const int KT = C::KG > 1 ? max(0, min(KTB - kg * KTL, KTL)) : KTB;  // of this group
 
   // this lane's wave loads: wl = wave + u * NW; A rows first, then B rows.
   // Lane (row rl = lane / 8 of the load, slot lane % 8) fetches logical chunk
@@ -435,7 +444,7 @@ __global__ __launch_bounds__(C::NT) void igemm2_conv(GemmArgs a) {
   const SegRt q1 = seg_rt<C::ESZ>(a.seg[1], P);
   const SegRt q2 = seg_rt<C::ESZ>(a.seg[2], P);
   const __amdgpu_buffer_rsrc_t rw = make_rsrc(a.Bw, (long)a.N * a.ldb * C::ESZ);
-  const uint32_t sbase = lds_u32(smem);
+  const uint32_t sbase = lds_u32(gsmem);
 
   // K position of the next stage to issue: segment, channel chunk and tap
   // (dy, dx), walked chunk-major (the taps of one 64-channel chunk run back
@@ -486,7 +495,7 @@ __global__ __launch_bounds__(C::NT) void igemm2_conv(GemmArgs a) {
 #pragma unroll
     for (int u = 0; u < C::NU; ++u) {
       const int wl = wave + u * C::NW;
-      char* dst = smem + stage_off + wl * 1024;  // 1 KB per wave load
+      char* dst = gsmem + stage_off + wl * 1024;  // 1 KB per wave load
       if (u < C::UA) {
         const uint32_t off = ((pmask[u] >> t9) & 1u)
                                  ? __umul24(ppix[u] + shift, pitch) + cbyte + coff[u]
@@ -524,12 +533,12 @@ __global__ __launch_bounds__(C::NT) void igemm2_conv(GemmArgs a) {
   // read one step ago, issue every fragment read of this stage, then the
   // MFMAs of each K-half once its fragments have landed.
   bf16x8_t af[C::KH][C::TM], bfr[C::KH][C::TN];
-  issue(0);
+  if (C::KG == 1 || KT > 0) issue(0);
 #pragma unroll
   for (int q = 1; q < C::STAGES - 1; ++q)
     if (q < KT) issue((uint32_t)(q * C::STAGE));
   int slot = 0;
-  for (int kt = 0; kt < KT; ++kt) {
+  for (int kt = 0; kt < KTL; ++kt) {
     // stages issued after this one: min(STAGES - 2, KT - 1 - kt), each NU
     // (or NU_LO) loads of this wave
     const int after = min(C::STAGES - 2, KT - 1 - kt);
@@ -538,25 +547,17 @@ __global__ __launch_bounds__(C::NT) void igemm2_conv(GemmArgs a) {
     else
       wait_stages<C::STAGES - 2, C::NU_LO>(after);
     __builtin_amdgcn_s_barrier();
+    if (C::KG > 1 && kt >= KT) continue;  // a shorter group keeps the barriers
     const uint32_t sb = sbase + (uint32_t)(slot * C::STAGE);
-    if constexpr (!C::RDF) {
-    // the slot refilled here was read one step ago: every wave is past that
-    if (kt + C::STAGES - 1 < KT) {
-      const int ns = slot + C::STAGES - 1;
-      issue((uint32_t)((ns >= C::STAGES ? ns - C::STAGES : ns) * C::STAGE));
-    }
-    }
 #pragma unroll
     for (int s = 0; s < C::KH; ++s) {
       ds_rd_n<C::TM, 16 * C::RB, 0>(af[s], sb + fa[s]);
       ds_rd_n<C::TN, 16 * C::RB, C::A_BYTES>(bfr[s], sb + fb[s]);
     }
-    if constexpr (C::RDF) {
     // the slot refilled here was read one step ago: every wave is past that
     if (kt + C::STAGES - 1 < KT) {
       const int ns = slot + C::STAGES - 1;
       issue((uint32_t)((ns >= C::STAGES ? ns - C::STAGES : ns) * C::STAGE));
-    }
     }
     slot = slot + 1 == C::STAGES ? 0 : slot + 1;
 #pragma unroll
@@ -577,6 +578,27 @@ __global__ __launch_bounds__(C::NT) void igemm2_conv(GemmArgs a) {
     __builtin_amdgcn_sched_barrier(0);
   }
   __syncthreads();
+  if constexpr (C::KG > 1) {
+    // the groups' sums meet in LDS, added to group 0's in group order
+    f32x4_t* ps = reinterpret_cast<f32x4_t*>(smem);
+    const int gt = tid - kg * C::NW * 64;
+#pragma unroll
+    for (int i = 0; i < C::TM; ++i)
+#pragma unroll
+      for (int j = 0; j < C::TN; ++j)
+        if (kg > 0) ps[(((kg - 1) * C::TM + i) * C::TN + j) * C::NW * 64 + gt] = acc[i][j];
+    __syncthreads();
+    if (kg == 0) {
+#pragma unroll
+      for (int q = 0; q < C::KG - 1; ++q)
+#pragma unroll
+        for (int i = 0; i < C::TM; ++i)
+#pragma unroll
+          for (int j = 0; j < C::TN; ++j)
+            acc[i][j] += ps[((q * C::TM + i) * C::TN + j) * C::NW * 64 + gt];
+    }
+    __syncthreads();
+  }
 
   // epilogue in 16-row slices: accumulators -> LDS -> 8-channel rows
   // (+bias, +rowvec, +residual) -> 16-byte stores.  With a.stats the stored
@@ -672,7 +694,7 @@ __global__ __launch_bounds__(C::NT) void igemm2_conv(GemmArgs a) {
   for (int g = 0; g < C::WAVES_M; ++g) {
 #pragma unroll
     for (int i = 0; i < C::TM; ++i) {
-      if (wm == g) acc16_to_lds<C::TM, C::TN, C::WN, C::LDC>(ct, wn, lane, i, acc);
+      if (wm == g && kg == 0) acc16_to_lds<C::TM, C::TN, C::WN, C::LDC>(ct, wn, lane, i, acc);
       __syncthreads();
       float rcur[NTK][8];
 #pragma unroll
@@ -1250,10 +1272,15 @@ __global__ void wgrad_finalize(GemmArgs a, int splits) {
 // ---------------------------------------------------------------------------
 
 namespace launch2 {
-using C2_128x160 = CfgC<128, 160, 64, 80, 2, 64, false, false>;   // 4 waves, two blocks per CU
-using C2_128x128 = CfgC<128, 128, 64, 64, 2, 64, false, false>;   // 4 waves, two blocks per CU
-using C2_128x192 = CfgC<128, 192, 64, 96, 2, 64, false, false>;   // 4 waves, two blocks per CU
-using C2_64x128S3 = CfgC<64, 128, 32, 64, 3, 64, false, false>;  // 4 waves, 3 stages, two blocks per CU
+using C2_128x160 = CfgC<128, 160, 64, 80>;   // 4 waves, two blocks per CU
+using C2_128x128 = CfgC<128, 128, 64, 64>;   // 4 waves, two blocks per CU
+using C2_128x192 = CfgC<128, 192, 64, 96>;   // 4 waves, two blocks per CU
+using C2_64x128S3 = CfgC<64, 128, 32, 64, 3>;  // 4 waves, 3 stages, two blocks per CU
+// grids that do not fill the GPU
+using C2_32x64 = CfgC<32, 64, 16, 32, 4>;
+using C2_32x64G2 = CfgC<32, 64, 16, 32, 3, 64, false, 2>;
+using C2_32x64G4 = CfgC<32, 64, 16, 32, 3, 64, false, 4>;
+using C2_64x64G2 = CfgC<64, 64, 32, 32, 3, 64, false, 2>;
 // channel counts that are multiples of 32 but not of 64: 32 channels per K-step
 using C2_128x160K32 = CfgC<128, 160, 64, 80, 4, 32>;
 using C2_128x128K32 = CfgC<128, 128, 64, 64, 4, 32>;
@@ -1364,6 +1391,10 @@ static auto with_conv(int t, F f) {
     case TILE2_C128x160: return f(C2_128x160());
     case TILE2_C128x192: return f(C2_128x192());
     case TILE2_C64x128S3: return f(C2_64x128S3());
+    case TILE2_C32x64: return f(C2_32x64());
+    case TILE2_C32x64G2: return f(C2_32x64G2());
+    case TILE2_C32x64G4: return f(C2_32x64G4());
+    case TILE2_C64x64G2: return f(C2_64x64G2());
     case TILE2_C128x160K32: return f(C2_128x160K32());
     case TILE2_C128x128K32: return f(C2_128x128K32());
     case TILE2_C64x96K32: return f(C2_64x96K32());

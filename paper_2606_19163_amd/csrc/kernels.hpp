@@ -91,7 +91,11 @@ enum Tile2 : int {
   TILE2_C128x128 = 1,   // 4 waves of 64 x 64, two blocks per CU
   TILE2_C128x192 = 2,   // 4 waves of 64 x 96, two blocks per CU
   TILE2_C64x128S3 = 3,  // 4 waves of 32 x 64, three LDS stages, two blocks per CU
-  TILE2_CONV_LAST = 3,  // of the 64-channel tiles
+  TILE2_C32x64 = 4,     // 4 waves of 16 x 32, four stages, three blocks per CU
+  TILE2_C32x64G2 = 5,   // the same in two K groups of 4 waves, three stages
+  TILE2_C32x64G4 = 6,   // the same in four
+  TILE2_C64x64G2 = 7,   // two K groups of 4 waves of 32 x 32, three stages
+  TILE2_CONV_LAST = 7,  // of the 64-channel tiles
   TILE2_C128x160K32 = 8,
   TILE2_C128x128K32 = 9,
   TILE2_C64x96K32 = 10,

@@ -16,6 +16,7 @@
 
 #include "error.hpp"
 #include "kernels.hpp"
+#include "plan.hpp"
 #include "pulse_stage.h"
 
 using namespace pulse;
@@ -188,6 +189,13 @@ struct pulse_stage {
   char* fwd_base = nullptr;
   size_t f_red = 0, f_e = 0, f_kpart = 0, f_kcap = 0;
   size_t fs_red = 0, fs_e = 0, fs_kpart = 0, fs_kcap = 0, fs_bytes = 0;  // compact layout
+  struct ConvPlanOf {
+    int N, K;
+    bool fwd;
+    ConvWant want;
+    ConvPlan plan;
+  };
+  std::vector<ConvPlanOf> plans;
   long fwd_part_cap = -1;  // forward partials (floats) that keep that layout in the static
                            // array; -1: it does not fit even without them
   float* fwd(size_t off) const { return reinterpret_cast<float*>(fwd_base + off); }
@@ -256,12 +264,10 @@ void layout_gn(const pulse_stage* s, GnSave& g, size_t& off, int C) {
   off += align256((size_t)s->geo.B * C * 4);
 }
 
-long conv_tiles(const pulse_stage* s, int tile, int N) {
-  const TileInfo ti = tile2_info(tile);
-  return ((s->P + ti.bm - 1) / ti.bm) * ((N + ti.bn - 1) / ti.bn);
-}
+long conv_tiles(const pulse_stage* s, int tile, int N) { return conv_tile_count(tile, s->P, N); }
 
-// Tile shape of a conv-mode GEMM with N output columns.
+// Tile shape of a conv-mode GEMM with N output columns, before the small-grid
+// plan of the 64-channel stages.
 int conv_tile(const pulse_stage* s, int N) {
   if (s->dtype == DT_F32) {
     // fp32 MFMAs bound these: the tile whose rounds of one block per CU cost
@@ -304,27 +310,50 @@ int wgrad_tile(const pulse_stage* s, int M, int N) {
   return M % 320 == 0 ? TILE2_W320x128 : TILE2_W128x128;
 }
 
-// K splits of a conv-mode GEMM: enough blocks for two per CU (the tile's
-// occupancy), each split keeping at least 4 K-steps.  The fp32 and the
-// 32-channel tiles pay about 7 us for the partials' finalize and so split
-// only long K: fp32 from 128 blocks down to fill the GPU once, 9 or more
-// K-steps per split (1 x 32 x 32, 128 -> 128: 12 us in two splits against
-// 15); 32-channel tiles to two blocks per CU, 18 or more K-steps per split
-// (3 x 27 x 45: 288 -> 96 16 us in four against 28 in one, 96 -> 288, 27
-// K-steps, 13 us in one against 17 in two).  `fwd` (a forward conv): the
-// partials of a stage whose forward scratch without them fits the static
-// scratch array leave it fitting.
-int conv_ksplit(const pulse_stage* s, int tile, int N, int K, bool fwd) {
+// Blocks of a conv-mode GEMM that fill the GPU: two per CU, one in fp32
+long conv_want(const pulse_stage* s) { return s->dtype == DT_F32 ? 256 : 512; }
+
+// K splits of a conv-mode GEMM on that tile: enough blocks to fill the GPU,
+// each split keeping at least 4 K-steps.  The fp32 and the 32-channel tiles
+// pay about 7 us for the partials' finalize and so split only long K: fp32
+// from 128 blocks down to fill the GPU once, 9 or more K-steps per split
+// (1 x 32 x 32, 128 -> 128: 12 us in two splits against 15); 32-channel
+// tiles to two blocks per CU, 18 or more K-steps per split (3 x 27 x 45:
+// 288 -> 96 16 us in four against 28 in one, 96 -> 288, 27 K-steps, 13 us in
+// one against 17 in two).
+int conv_ksplit(const pulse_stage* s, int tile, int N, int K) {
   const TileInfo ti = tile2_info(tile);
   const long tiles = conv_tiles(s, tile, N);
   const long kt = K / ti.bk;
-  const bool few = s->dtype == DT_F32 || !s->k64;
-  const long want = s->dtype == DT_F32 ? 256 : 512;
-  if (tiles >= want || (s->dtype == DT_F32 && tiles > 128)) return 1;
-  long ks = few ? want / tiles : (want + tiles - 1) / tiles;
-  ks = std::min(ks, std::max(1L, kt / (s->dtype == DT_F32 ? 9 : s->k64 ? 4 : 18)));
-  if (fwd && few && s->fwd_part_cap >= 0) ks = std::min(ks, std::max(1L, s->fwd_part_cap / (s->P * N)));
+  const bool f32 = s->dtype == DT_F32;
+  const long want = conv_want(s);
+  if (tiles >= want || (f32 && tiles > 128)) return 1;
+  long ks = s->k64 && !f32 ? (want + tiles - 1) / tiles : want / tiles;
+  ks = std::min(ks, std::max(1L, kt / (f32 ? 9 : s->k64 ? 4 : 18)));
   return (int)std::min(ks, (long)s->conv_ksplit_cap);
+}
+
+// Tile and K split of a conv-mode GEMM.  64-channel bf16 stages take the
+// small-grid plan where the 128-row tiles do not even give every CU a block.
+// `fwd` (a forward conv): the partials of a stage that the static forward
+// scratch holds keep it there (fwd_part_cap).
+ConvPlan make_conv_plan(const pulse_stage* s, int N, int K, bool fwd, ConvWant want) {
+  const int tile = conv_tile(s, N);
+  const long cap = fwd ? s->fwd_part_cap : -1;
+  if (s->dtype == DT_BF16 && s->k64 && s->conv_tile_force < 0 && conv_tiles(s, tile, N) < 256)
+    return conv_plan_small(s->P, N, K, s->geo.hw(), tile, s->conv_ksplit_cap, cap,
+                           want == CONV_GNB && s->no_gnb ? CONV_PLAIN : want);
+  long ks = conv_ksplit(s, tile, N, K);
+  if (cap >= 0) ks = std::min(ks, std::max(1L, cap / (s->P * N)));
+  return conv_plan_of(tile, ks, K);
+}
+
+// The plan of every launch, made when the stage is created.
+const ConvPlan& conv_plan(pulse_stage* s, int N, int K, bool fwd, ConvWant want) {
+  for (const auto& p : s->plans)
+    if (p.N == N && p.K == K && p.fwd == fwd && p.want == want) return p.plan;
+  s->plans.push_back({N, K, fwd, want, make_conv_plan(s, N, K, fwd, want)});
+  return s->plans.back().plan;
 }
 
 // Pixel split of a weight-gradient GEMM.  With s splits the grid holds
@@ -496,15 +525,10 @@ pulse_status build_layout(pulse_stage* s) {
       for (int c : {b.cin, b.cout}) {
         RedGrid rg = red_grid(s->geo, c);
         red = std::max(red, (size_t)s->geo.B * rg.chunks * 2 * c);
-        // conv-mode K-split partials (an upper bound over the K of each launch)
-        const int ks = conv_ksplit(s, conv_tile(s, c), c, 1 << 30, false);
-        if (ks > 1) kpart = std::max(kpart, (size_t)ks * s->P * c);
       }
     }
   s->part_cap = part;
   s->s_part = sc; sc += align256(part * 4);
-  s->kpart_cap = kpart;
-  s->s_kpart = sc; sc += align256(kpart * 4);
   s->red_cap = red;
   s->s_red = sc; sc += align256(red * 4);
   s->s_red2 = sc; sc += align256(red * 4);  // reductions on the side stream
@@ -519,25 +543,42 @@ pulse_status build_layout(pulse_stage* s) {
   const size_t nblk = std::max(s->eb.size(), s->db.size());
   s->s_e = sc; sc += align256(nblk * s->geo.B * cmax * 4);
   s->s_zero = sc; sc += 256;  // zero bytes read in place of out-of-image taps
-  s->ws_bytes = s->off_scratch + sc;
-  // the forward's scratch without conv partials, packed
-  // (pulse_stage_forward_static)
+  // the forward's scratch, packed (pulse_stage_forward_static): without conv
+  // partials, then with the forward convs' own.  A stage that fits the static
+  // array with the plain plan (its tile and K split) keeps fitting it.
   size_t fs = 0;
   s->fs_red = fs; fs += align256(red * 4);
   s->fs_e = fs; fs += align256(nblk * s->geo.B * cmax * 4);
   s->fs_kpart = fs;
-  s->fwd_part_cap = fs <= PULSE_FWD_STATIC_SCRATCH_BYTES
+  size_t plain = 0;
+  if (s->dtype == DT_BF16 && s->k64)
+    for (auto* v : {&s->eb, &s->db})
+      for (auto& b : *v)
+        for (int K : {9 * b.cin, b.ldb2}) {
+          const int ks = conv_ksplit(s, conv_tile(s, b.cout), b.cout, K);
+          if (ks > 1) plain = std::max(plain, (size_t)ks * s->P * b.cout);
+        }
+  s->fwd_part_cap = fs + align256(plain * 4) <= PULSE_FWD_STATIC_SCRATCH_BYTES
                         ? (long)(PULSE_FWD_STATIC_SCRATCH_BYTES - fs) / 4 : -1;
-  // and with the K-split partials of the forward convs only, at their own K
+  // conv K-split partials: every launch's plan
   size_t fkpart = 0;
   for (auto* v : {&s->eb, &s->db})
     for (auto& b : *v) {
-      const int k2 = 9 * b.cout + (b.conv_sc ? b.cin : 0);
-      for (int K : {9 * b.cin, k2}) {
-        const int ks = conv_ksplit(s, conv_tile(s, b.cout), b.cout, K, true);
-        if (ks > 1) fkpart = std::max(fkpart, (size_t)ks * s->P * b.cout);
-      }
+      auto need = [&](int N, int K, bool fwd, ConvWant want) {
+        const ConvPlan p = conv_plan(s, N, K, fwd, want);
+        const size_t n = p.ks > 1 ? (size_t)p.ks * s->P * N : 0;
+        kpart = std::max(kpart, n);
+        if (fwd) fkpart = std::max(fkpart, n);
+      };
+      need(b.cout, 9 * b.cin, true, CONV_STATS);
+      for (ConvWant w : {CONV_PLAIN, CONV_STATS}) need(b.cout, b.ldb2, true, w);
+      need(b.cout, 9 * b.cout, false, CONV_GNB);
+      need(b.cin, b.cout, false, CONV_PLAIN);
+      need(b.cin, 9 * b.cout, false, CONV_GNB);
     }
+  s->kpart_cap = kpart;
+  s->s_kpart = sc; sc += align256(kpart * 4);
+  s->ws_bytes = s->off_scratch + sc;
   fs += align256(fkpart * 4);
   s->fs_kcap = fkpart;
   s->fs_bytes = fs;
@@ -740,13 +781,12 @@ double conv_bytes(const pulse_stage* s, const GemmArgs& a) {
 pulse_status run_conv(pulse_stage* s, GemmArgs& a, hipStream_t st, bool fwd,
                       int* stats_chunks) {
   if (stats_chunks) *stats_chunks = 0;
-  const int tile = conv_tile(s, a.N);
-  const int ks = conv_ksplit(s, tile, a.N, a.K, fwd);
-  const int kt = a.K / tile2_info(tile).bk;
-  a.ksplit = ks;
-  a.ksteps = (kt + ks - 1) / ks;
-  if (ks > 1) {
-    a.ksplit = (kt + a.ksteps - 1) / a.ksteps;  // no empty split
+  const ConvPlan plan = conv_plan(
+      s, a.N, a.K, fwd, stats_chunks ? (a.gnb ? CONV_GNB : a.stats ? CONV_STATS : CONV_PLAIN) : CONV_PLAIN);
+  const int tile = plan.tile;
+  a.ksplit = plan.ks;
+  a.ksteps = plan.ksteps;
+  if (a.ksplit > 1) {
     if ((size_t)a.ksplit * a.M * a.N > s->f_kcap)
       return fail(PULSE_E_SHAPE, "internal: conv partial buffer too small");
     a.part = s->fwd(s->f_kpart);
@@ -1150,7 +1190,7 @@ pulse_status block_backward(pulse_stage* s, int r, const Block& b, const VIn& xi
                     vnone(), dxs, nullptr, dt, st);
   };
   const bool sc_first =
-      b.conv_sc && conv_ksplit(s, conv_tile(s, b.cout), b.cout, 9 * b.cout, false) == 1;
+      b.conv_sc && conv_tiles(s, conv_tile(s, b.cout), b.cout) >= conv_want(s);
   if (sc_first) {
     if ((ps = shortcut_dgrad()) != PULSE_OK) return ps;
     s->fork_attached = false;  // the fork below orders the side stream after it

@@ -23,6 +23,7 @@
 
 #include "error.hpp"
 #include "kernels.hpp"
+#include "plan.hpp"
 #include "pulse_tstage.h"
 #include "tkernels.hpp"
 
@@ -206,48 +207,35 @@ int env_or(const char* name, int dflt) {
 // needs more than one round of 128-row tiles takes 128 x 192 (from the
 // sweep of the 1024-token, 1408-wide stage: +13 % step against 64 x 128);
 // otherwise 64 x 128 tiles with a three-stage LDS ring (two blocks per CU),
-// no K split: with 16 MFMAs per wave and K-step the deeper ring hides the
+// no K split where they give every CU a block: with 16 MFMAs per wave and K-step the deeper ring hides the
 // operand latency that two stages leave exposed, and beats splitting K.
 // Overrides (for sweeps): PULSE_TCONV_TILE forces a tile (with the split
 // rule of two blocks per CU, at least 4 K-steps per split),
 // PULSE_TCONV_KSPLIT_MAX caps the split.
-struct ConvPlan {
-  int tile, ks, ksteps;
-};
-
-long tile_count(int tile, long M, int N) {
-  const TileInfo ti = tile2_info(tile);
-  return ((M + ti.bm - 1) / ti.bm) * ((N + ti.bn - 1) / ti.bn);
-}
-
 ConvPlan tconv_plan(int tile_force, int ks_cap, long M, int N, int K) {
-  ConvPlan p;
-  long ks = 1;
+  ks_cap = std::max(1, ks_cap);
   if (tile_force >= 0) {
-    p.tile = tile_force;
-    const long tiles = tile_count(p.tile, M, N);
-    const long kt = K / tile2_info(p.tile).bk;
-    if (tiles < 512) {
-      ks = (512 + tiles - 1) / tiles;
-      ks = std::min(ks, std::max(1L, kt / 4));
-    }
-  } else {
-    p.tile = -1;
-    long best = 0;
-    for (int t : {TILE2_C128x192, TILE2_C128x160, TILE2_C128x128}) {
-      const long n = tile_count(t, M, N);
-      if (n <= 512 && n >= 400 && n > best) {
-        best = n;
-        p.tile = t;
-      }
-    }
-    if (p.tile < 0) p.tile = tile_count(TILE2_C128x192, M, N) > 512 ? TILE2_C128x192 : TILE2_C64x128S3;
+    const long tiles = conv_tile_count(tile_force, M, N);
+    const long kt = K / tile2_info(tile_force).bk;
+    long ks = 1;
+    if (tiles < 512) ks = std::min((512 + tiles - 1) / tiles, std::max(1L, kt / 4));
+    return conv_plan_of(tile_force, std::min(ks, (long)ks_cap), K);
   }
-  ks = std::min(ks, (long)std::max(1, ks_cap));
-  const long kt = K / tile2_info(p.tile).bk;
-  p.ksteps = (int)((kt + ks - 1) / ks);
-  p.ks = (int)((kt + p.ksteps - 1) / p.ksteps);  // no empty split
-  return p;
+  int tile = -1;
+  long best = 0;
+  for (int t : {TILE2_C128x192, TILE2_C128x160, TILE2_C128x128}) {
+    const long n = conv_tile_count(t, M, N);
+    if (n <= 512 && n >= 400 && n > best) {
+      best = n;
+      tile = t;
+    }
+  }
+  if (tile < 0)
+    tile = conv_tile_count(TILE2_C128x192, M, N) > 512 ? TILE2_C128x192 : TILE2_C64x128S3;
+  // fewer 64 x 128 tiles than CUs: smaller tiles, K groups or a K split
+  if (tile == TILE2_C64x128S3 && conv_tile_count(tile, M, N) < 256)
+    return conv_plan_small(M, N, K, 1, TILE2_C64x128S3, ks_cap, -1, CONV_PLAIN);
+  return conv_plan_of(tile, 1, K);
 }
 
 // weight-gradient tile for M rows summed over P tokens (PULSE_TWGRAD_TILE

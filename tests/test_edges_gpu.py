@@ -51,3 +51,26 @@ CONV_EDGES = [
                          ids=[f"{d}-{b}x{h}x{w}x{c}" for d, b, h, w, c, _, _ in CONV_EDGES])
 def test_conv_tiles(dtype, batch, h, w, c, groups, n):
     _parity(_pair(batch, h, w, c, groups, 64, dtype, n), 22, f"{dtype} {batch}x{h}x{w}x{c}")
+
+
+# grids that do not fill the GPU: every small tile and K grouping is picked by
+# some conv of these stages, with ragged rows, K splits whose last split and
+# last K group are shorter, and images smaller and larger than a tile
+SMALL = [(1, 3, 5, 64, 1), (2, 8, 8, 640, 1), (1, 16, 16, 320, 2), (3, 9, 7, 448, 1),
+         (2, 24, 24, 128, 1), (1, 40, 36, 192, 1), (4, 16, 16, 512, 1)]
+
+
+@pytest.mark.parametrize("batch,h,w,c,n", SMALL, ids=[f"{b}x{h}x{w}x{c}" for b, h, w, c, _ in SMALL])
+def test_small_grids(batch, h, w, c, n):
+    _parity(_pair(batch, h, w, c, 32, 64, configs.BF16, n), 23, f"small {batch}x{h}x{w}x{c}")
+
+
+@pytest.mark.parametrize("tile", [4, 5, 6, 7])
+@pytest.mark.parametrize("batch,h,w", [(2, 12, 10), (2, 16, 8)])
+def test_small_tiles_forced(monkeypatch, tile, batch, h, w):
+    """Each small tile on every conv of a stage: K shorter than its groups'
+    pipeline (the 1x1 shortcut), epilogue statistics and GroupNorm-backward
+    sums (128-pixel images hold whole tiles) and ragged rows."""
+    monkeypatch.setenv("PULSE_CONV_TILE", str(tile))
+    monkeypatch.setenv("PULSE_CONV_KSPLIT_MAX", "1")
+    _parity(_pair(batch, h, w, 128, 32, 64, configs.BF16, 1), 24, f"tile{tile}")
