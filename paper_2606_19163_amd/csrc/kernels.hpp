@@ -9,6 +9,12 @@
 
 namespace pulse {
 
+// Events that only order kernels of one GPU: no timing, and no system-scope
+// cache flush when they complete (a few microseconds on the recording
+// stream); the host sees results through its own synchronisation of the
+// caller's stream.
+constexpr unsigned ORDER_EVENT = hipEventDisableTiming | hipEventDisableSystemFence;
+
 constexpr int MAX_SEG = 3;
 
 // A contiguous range of the implicit operand: K in CONV mode, N in WGRAD

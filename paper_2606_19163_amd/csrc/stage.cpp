@@ -1561,15 +1561,15 @@ pulse_status pulse_stage_bind(pulse_stage* s, const float* params, float* grads,
                 s->ws_bytes);
   if (pulse_stage_inflight(s) > 0)
     return fail(PULSE_E_STATE, "cannot rebind with microbatches in flight");
-  if (!s->ev_last) HIPCHK(hipEventCreateWithFlags(&s->ev_last, hipEventDisableTiming));
+  if (!s->ev_last) HIPCHK(hipEventCreateWithFlags(&s->ev_last, ORDER_EVENT));
   if (!s->side && env_int("PULSE_SERIAL", 0) == 0) {
     // default priority, no implicit synchronisation with the null stream
     HIPCHK(hipStreamCreateWithFlags(&s->side, hipStreamNonBlocking));
-    HIPCHK(hipEventCreateWithFlags(&s->ev_fork, hipEventDisableTiming));
-    HIPCHK(hipEventCreateWithFlags(&s->ev_join, hipEventDisableTiming));
+    HIPCHK(hipEventCreateWithFlags(&s->ev_fork, ORDER_EVENT));
+    HIPCHK(hipEventCreateWithFlags(&s->ev_join, ORDER_EVENT));
     for (int i = 0; i < 2; ++i) {
-      HIPCHK(hipEventCreateWithFlags(&s->ev_w2[i], hipEventDisableTiming));
-      HIPCHK(hipEventCreateWithFlags(&s->ev_w1[i], hipEventDisableTiming));
+      HIPCHK(hipEventCreateWithFlags(&s->ev_w2[i], ORDER_EVENT));
+      HIPCHK(hipEventCreateWithFlags(&s->ev_w1[i], ORDER_EVENT));
     }
   }
   s->prm = params;

@@ -629,7 +629,7 @@ struct BwdSync {
 hipEvent_t sync_event(pulse_tstage* s) {
   if (s->sev_used == s->sev.size()) {
     hipEvent_t e;
-    if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) return nullptr;
+    if (hipEventCreateWithFlags(&e, ORDER_EVENT) != hipSuccess) return nullptr;
     s->sev.push_back(e);
   }
   return s->sev[s->sev_used++];
@@ -876,7 +876,7 @@ pulse_status pulse_tstage_bind(pulse_tstage* s, const float* params, float* grad
   if (!s->side && env_or("PULSE_SERIAL", 0) == 0) {
     // default priority, no implicit synchronisation with the null stream
     THIP(hipStreamCreateWithFlags(&s->side, hipStreamNonBlocking));
-    THIP(hipEventCreateWithFlags(&s->ev_settle, hipEventDisableTiming));
+    THIP(hipEventCreateWithFlags(&s->ev_settle, ORDER_EVENT));
   }
   s->prm = params;
   s->grd = grads;
