@@ -32,14 +32,16 @@ hipError_t launch_attn_bwd(const void* qkv, const void* o, const void* dout, con
 // y = LN(x) * g + b per token; stats[2 t] = mean, stats[2 t + 1] = rstd.
 hipError_t launch_ln_fwd(const void* x, long T, int C, float eps, const float* g, const float* b,
                          void* y, float* stats, hipStream_t st);
-// dx = add + d LN / dx (add [T][C] bf16 or null); part[ln_bwd_blocks(T)][2][C]
-// receives per-block sums of dy * xhat (row 0) and dy (row 1); csum (or
-// null), [ln_bwd_blocks(T)][2][C], per-block column sums of dx as stored in
-// row 0.
+// dx = add + d LN / dx (add [T][C] bf16 or null); part[ln_bwd_blocks(T)][3][C]
+// receives per-block column sums of dy * xhat, dy and dx as stored.  done
+// (may be null): an event recorded by the kernel's own completion.
 int ln_bwd_blocks(long T);
 hipError_t launch_ln_bwd(const void* dy, const void* x, const float* stats, const float* g,
-                         const void* add, long T, int C, void* dx, float* part, float* csum,
-                         hipStream_t st);
+                         const void* add, long T, int C, void* dx, float* part, hipStream_t st,
+                         hipEvent_t done = nullptr);
+// dg += row 0, db += row 1, dsum (or null) += row 2 of part[rows][3][C]
+hipError_t launch_ln_totals(const float* part, int rows, int C, float* dg, float* db, float* dsum,
+                            hipStream_t st);
 
 // m = GELU(z) (erf form), n % 8 == 0 elements
 hipError_t launch_gelu_fwd(const void* z, void* m, long n, hipStream_t st);

@@ -1,7 +1,10 @@
 // LayerNorm and GELU of the transformer-block stage (gfx950): token-major
 // [T][C] bf16 activations; one wave per token for the LayerNorm, each lane
 // holding whole 8-channel vectors in registers; statistics in fp32.
+#include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
+
+#include <algorithm>
 
 #include "common.hpp"
 #include "tkernels.hpp"
@@ -11,7 +14,7 @@ namespace pulse {
 namespace {
 
 constexpr int LN_VEC = 4;        // 8-channel vectors per lane: C <= 64 * 8 * LN_VEC = 2048
-constexpr int LN_TOK = 1;        // tokens per wave in the backward pass
+constexpr int LN_BLOCKS = 512;   // of the backward pass: two per CU
 
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
@@ -19,14 +22,17 @@ __device__ __forceinline__ float wave_sum(float v) {
   return v;
 }
 
-__device__ __forceinline__ void ld8bf(const uint16_t* p, float v[8]) {
-  const uint4 q = *reinterpret_cast<const uint4*>(p);
+__device__ __forceinline__ void up8bf(const uint4& q, float v[8]) {
   const uint32_t w[4] = {q.x, q.y, q.z, q.w};
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     v[2 * i] = __uint_as_float(w[i] << 16);
     v[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
   }
+}
+
+__device__ __forceinline__ void ld8bf(const uint16_t* p, float v[8]) {
+  up8bf(*reinterpret_cast<const uint4*>(p), v);
 }
 
 __device__ __forceinline__ void st8bf(uint16_t* p, const float v[8]) {
@@ -81,117 +87,142 @@ __global__ __launch_bounds__(256) void k_ln_fwd(const uint16_t* x, long T, int C
   if (lane == 0) stats[t] = make_float2(mean, rstd);
 }
 
-// dx = add + rstd * (dxh - mean(dxh) - xh * mean(dxh * xh)), dxh = dy * g;
-// per-block partial sums of dy * xh (row 0) and dy (row 1) over the block's
-// tokens go to part[block][2][C]
+// dx = add + rstd * (dxh - mean(dxh) - xh * mean(dxh * xh)), dxh = dy * g.
+// A wave takes every (4 x blocks)-th token, the next token's rows in flight
+// while the current one is reduced, and keeps its column sums of dy * xh, dy
+// and dx (as stored) in registers over its tokens; the block's four waves
+// meet in LDS and part[block][3][C] receives those sums.  Bound by HBM (three
+// rows read, one written per token).  NV, the 8-channel vectors per lane, is
+// the width's own: with registers for 2048 channels and one token per wave,
+// 4096 tokens of 768 channels wrote as many bytes of partials as of
+// activations and found little room beside the weight GEMMs of the other
+// stream: 34.6 us there on average against 16.5 now (10 us alone; 1408
+// channels, 8192 tokens: 39 -> 31 us alone).
+template <int NV>
 __global__ __launch_bounds__(256) void k_ln_bwd(const uint16_t* dy, const uint16_t* x,
                                                 const float2* stats, const float* g,
                                                 const uint16_t* add, long T, int C, uint16_t* dx,
-                                                float* part, float* csum) {
-  // per wave, [2][C / 4 per j] reused below; the partial-sum passes write
-  // lanes * 8 values per row whatever LN_VEC is
-  static_assert(64 * LN_VEC * 8 / 4 >= 64 * 8, "k_ln_bwd: LDS rows hold 64 lanes x 8 values");
-  __shared__ float sm[4][2][64 * LN_VEC * 8 / 4];
+                                                float* part) {
+  __shared__ float sm[3][4][64 * 8];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int nv = C / 8;
-  float accg[LN_VEC][8], accb[LN_VEC][8], accx[LN_VEC][8];
+  const long step = (long)gridDim.x * 4;
+  float acc[3][NV][8];
 #pragma unroll
-  for (int j = 0; j < LN_VEC; ++j)
+  for (int r = 0; r < 3; ++r)
 #pragma unroll
-    for (int i = 0; i < 8; ++i) accg[j][i] = accb[j][i] = accx[j][i] = 0.f;
-  for (int k = 0; k < LN_TOK; ++k) {
-    const long t = ((long)blockIdx.x * 4 + w) * LN_TOK + k;
-    if (t >= T) break;
-    const float2 st = stats[t];
-    float xh[LN_VEC][8], gy[LN_VEC][8];
+    for (int j = 0; j < NV; ++j)
+#pragma unroll
+      for (int i = 0; i < 8; ++i) acc[r][j][i] = 0.f;
+  uint4 xr[NV], dr[NV], ar[NV];
+  float2 st = make_float2(0.f, 0.f);
+  auto load = [&](long t) __attribute__((always_inline)) {
+    st = stats[t];
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+      const int vi = min(lane + 64 * j, nv - 1);  // lanes past the row reload its end
+      xr[j] = *reinterpret_cast<const uint4*>(x + t * C + vi * 8);
+      dr[j] = *reinterpret_cast<const uint4*>(dy + t * C + vi * 8);
+      if (add) ar[j] = *reinterpret_cast<const uint4*>(add + t * C + vi * 8);
+    }
+  };
+  long t = (long)blockIdx.x * 4 + w;
+  if (t < T) load(t);
+  for (; t < T; t += step) {
+    float xh[NV][8], gy[NV][8], a[NV][8];
     float s1 = 0.f, s2 = 0.f;
+    const float rs = st.y;
 #pragma unroll
-    for (int j = 0; j < LN_VEC; ++j) {
+    for (int j = 0; j < NV; ++j) {
       const int vi = lane + 64 * j;
+      float dv[8];
+      up8bf(xr[j], xh[j]);
+      up8bf(dr[j], dv);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) a[j][i] = 0.f;
+      if (add) up8bf(ar[j], a[j]);
       if (vi < nv) {
-        float xv[8], dv[8];
-        ld8bf(x + t * C + vi * 8, xv);
-        ld8bf(dy + t * C + vi * 8, dv);
+        const float4 g0 = reinterpret_cast<const float4*>(g)[2 * vi];
+        const float4 g1 = reinterpret_cast<const float4*>(g)[2 * vi + 1];
+        const float gv[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-          xh[j][i] = (xv[i] - st.x) * st.y;
-          gy[j][i] = dv[i] * g[vi * 8 + i];
+          xh[j][i] = (xh[j][i] - st.x) * rs;
+          gy[j][i] = dv[i] * gv[i];
           s1 += gy[j][i];
           s2 += gy[j][i] * xh[j][i];
-          accg[j][i] += dv[i] * xh[j][i];
-          accb[j][i] += dv[i];
+          acc[0][j][i] += dv[i] * xh[j][i];
+          acc[1][j][i] += dv[i];
         }
       }
     }
+    if (t + step < T) load(t + step);
     const float m1 = wave_sum(s1) / C, m2 = wave_sum(s2) / C;
 #pragma unroll
-    for (int j = 0; j < LN_VEC; ++j) {
+    for (int j = 0; j < NV; ++j) {
       const int vi = lane + 64 * j;
       if (vi < nv) {
-        float o[8], a[8];
-        if (add) {
-          ld8bf(add + t * C + vi * 8, a);
-        } else {
-#pragma unroll
-          for (int i = 0; i < 8; ++i) a[i] = 0.f;
-        }
+        float o[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-          o[i] = a[i] + st.y * (gy[j][i] - m1 - xh[j][i] * m2);
-          accx[j][i] += bf2f(f2bf(o[i]));  // the value as stored
+          o[i] = a[j][i] + rs * (gy[j][i] - m1 - xh[j][i] * m2);
+          acc[2][j][i] += bf2f(f2bf(o[i]));  // the value as stored
         }
         st8bf(dx + t * C + vi * 8, o);
       }
     }
   }
-  // the four waves' channel sums, in wave order, one vector slice at a time
-  float* out = part + (long)blockIdx.x * 2 * C;
+  // the four waves' column sums, in wave order, one vector slice at a time
+  float* out = part + (long)blockIdx.x * 3 * C;
 #pragma unroll
-  for (int j = 0; j < LN_VEC; ++j) {
-    const int vi = lane + 64 * j;
+  for (int j = 0; j < NV; ++j) {
+    if (j) __syncthreads();
+#pragma unroll
+    for (int r = 0; r < 3; ++r)
+#pragma unroll
+      for (int i = 0; i < 8; ++i) sm[r][w][lane + 64 * i] = acc[r][j][i];
     __syncthreads();
+    for (int e = threadIdx.x; e < 3 * 512; e += 256) {
+      const int r = e >> 9, c = e & 511;  // column c of this slice
+      if (j * 512 + c >= C) continue;
+      const int at = (c >> 3) + 64 * (c & 7);
+      float s = sm[r][0][at];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      sm[w][0][lane * 8 + i] = accg[j][i];
-      sm[w][1][lane * 8 + i] = accb[j][i];
-    }
-    __syncthreads();
-    if (w == 0 && vi < nv) {
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        float sg = 0.f, sb = 0.f;
-#pragma unroll
-        for (int ww = 0; ww < 4; ++ww) {
-          sg += sm[ww][0][lane * 8 + i];
-          sb += sm[ww][1][lane * 8 + i];
-        }
-        out[vi * 8 + i] = sg;
-        out[C + vi * 8 + i] = sb;
-      }
-    }
-  }
-  if (!csum) return;
-  // column sums of dx as stored, to csum[block][0][C]
-  float* cs = csum + (long)blockIdx.x * 2 * C;
-#pragma unroll
-  for (int j = 0; j < LN_VEC; ++j) {
-    const int vi = lane + 64 * j;
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < 8; ++i) sm[w][0][lane * 8 + i] = accx[j][i];
-    __syncthreads();
-    if (w == 0 && vi < nv) {
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        float sx = 0.f;
-#pragma unroll
-        for (int ww = 0; ww < 4; ++ww) sx += sm[ww][0][lane * 8 + i];
-        cs[vi * 8 + i] = sx;
-      }
+      for (int ww = 1; ww < 4; ++ww) s += sm[r][ww][at];
+      out[(long)r * C + j * 512 + c] = s;
     }
   }
 }
 
+// dg += row 0, db += row 1, dsum (or null) += row 2 of part[rows][3][C]: 8
+// columns x 32 row lanes per block, each lane's rows in ascending order (8
+// loads in flight), the lanes in a fixed tree.
+__global__ __launch_bounds__(256) void k_ln_totals(const float* part, int rows, int C, float* dg,
+                                                   float* db, float* dsum) {
+  __shared__ float sm[32][8];
+  const int tx = threadIdx.x & 7, ty = threadIdx.x >> 3;
+  const int r = blockIdx.y, c = blockIdx.x * 8 + tx;
+  const float* p = part + (long)r * C + c;
+  float s = 0.f;
+  constexpr int NB = 8;
+  for (int i0 = ty; i0 < rows; i0 += NB * 32) {
+    float v[NB];
+#pragma unroll
+    for (int k = 0; k < NB; ++k) v[k] = i0 + 32 * k < rows ? p[(long)(i0 + 32 * k) * 3 * C] : 0.f;
+#pragma unroll
+    for (int k = 0; k < NB; ++k) s += v[k];
+  }
+  sm[ty][tx] = s;
+  __syncthreads();
+  for (int off = 16; off > 0; off >>= 1) {
+    if (ty < off) sm[ty][tx] += sm[ty + off][tx];
+    __syncthreads();
+  }
+  if (ty == 0) {
+    float* dst = r == 0 ? dg : (r == 1 ? db : dsum);
+    dst[c] += sm[0][tx];
+  }
+}
 
 __global__ __launch_bounds__(256) void k_gelu_fwd(const uint16_t* z, uint16_t* m, long n8) {
   for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n8;
@@ -224,7 +255,7 @@ unsigned grid_of(long n, long cap = 8192) {
 
 }  // namespace
 
-int ln_bwd_blocks(long T) { return (int)((T + 4 * LN_TOK - 1) / (4 * LN_TOK)); }
+int ln_bwd_blocks(long T) { return (int)std::min<long>((T + 3) / 4, LN_BLOCKS); }
 
 hipError_t launch_ln_fwd(const void* x, long T, int C, float eps, const float* g, const float* b,
                          void* y, float* stats, hipStream_t st) {
@@ -236,13 +267,29 @@ hipError_t launch_ln_fwd(const void* x, long T, int C, float eps, const float* g
 }
 
 hipError_t launch_ln_bwd(const void* dy, const void* x, const float* stats, const float* g,
-                         const void* add, long T, int C, void* dx, float* part, float* csum,
-                         hipStream_t st) {
+                         const void* add, long T, int C, void* dx, float* part, hipStream_t st,
+                         hipEvent_t done) {
   if (C % 8 || C > 64 * 8 * LN_VEC) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_ln_bwd, dim3((unsigned)ln_bwd_blocks(T)), dim3(256), 0, st,
-                     static_cast<const uint16_t*>(dy), static_cast<const uint16_t*>(x),
-                     reinterpret_cast<const float2*>(stats), g, static_cast<const uint16_t*>(add),
-                     T, C, static_cast<uint16_t*>(dx), part, csum);
+  auto kern = C <= 512 ? k_ln_bwd<1> : C <= 1024 ? k_ln_bwd<2> : C <= 1536 ? k_ln_bwd<3>
+                                                                            : k_ln_bwd<4>;
+  const dim3 grid((unsigned)ln_bwd_blocks(T)), block(256);
+  const uint16_t* d = static_cast<const uint16_t*>(dy);
+  const uint16_t* xi = static_cast<const uint16_t*>(x);
+  const float2* ss = reinterpret_cast<const float2*>(stats);
+  const uint16_t* ad = static_cast<const uint16_t*>(add);
+  uint16_t* o = static_cast<uint16_t*>(dx);
+  if (done)  // the event completes with the kernel (no marker packet of its own)
+    hipExtLaunchKernelGGL(kern, grid, block, 0, st, nullptr, done, 0, d, xi, ss, g, ad, T, C, o,
+                          part);
+  else
+    hipLaunchKernelGGL(kern, grid, block, 0, st, d, xi, ss, g, ad, T, C, o, part);
+  return hipGetLastError();
+}
+
+hipError_t launch_ln_totals(const float* part, int rows, int C, float* dg, float* db, float* dsum,
+                            hipStream_t st) {
+  hipLaunchKernelGGL(k_ln_totals, dim3(C / 8, dsum ? 3 : 2), dim3(256), 0, st, part, rows, C, dg,
+                     db, dsum);
   return hipGetLastError();
 }
 

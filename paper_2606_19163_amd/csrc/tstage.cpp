@@ -115,10 +115,11 @@ struct pulse_tstage {
          s_wpart = 0, s_red = 0, s_zero = 0;
   size_t kpart_cap = 0, wpart_cap = 0, red_cap = 0;
   size_t s_red2 = 0;  // reduction buffer of the side stream
-  // column-sum partials of dh (LN2 backward) and of a decoder block's
-  // skip-linear output gradient (LN1 backward): the bias gradients of proj
-  // and skip without another pass over them
-  size_t s_cs_h[2] = {0, 0}, s_cs_x[2] = {0, 0};
+  // column-sum partials of the LayerNorm backward, per block parity: LN2's
+  // (its gains and dh, the bias gradient of proj), a decoder block's LN1's
+  // (its gains and the skip linear's output gradient, whose bias gradient it
+  // is) and an encoder block's LN1's (its gains); the side stream sums them
+  size_t s_cs_h[2] = {0, 0}, s_cs_x[2] = {0, 0}, s_cs_e[2] = {0, 0};
   // side stream: the weight-gradient GEMMs and bias-gradient sums of the
   // backward pass run on it, concurrently with the data-gradient chain
   hipStream_t side = nullptr;
@@ -372,16 +373,15 @@ void build_layout(pulse_tstage* s) {
   s->wpart_cap = wcap;
   s->s_kpart = take(std::max<size_t>(kcap, 4) * 4);
   s->s_wpart = take(std::max<size_t>(wcap, 4) * 4);
-  // reductions: LayerNorm partials [blocks][2][C] and bias-gradient chunk
-  // partials [chunks <= 128][2][N <= max(3C, R)]
-  const size_t red = std::max((size_t)ln_bwd_blocks(T) * 2 * C,
-                              (size_t)128 * 2 * std::max(3 * C, R));
+  // reductions: bias-gradient chunk partials [chunks <= 128][2][N <= max(3C, R)]
+  const size_t red = (size_t)128 * 2 * std::max(3 * C, R);
   s->red_cap = red;
   s->s_red = take(red * 4);
   s->s_red2 = take(red * 4);
   for (int i = 0; i < 2; ++i) {
-    s->s_cs_h[i] = take((size_t)ln_bwd_blocks(T) * 2 * C * 4);
-    s->s_cs_x[i] = take((size_t)ln_bwd_blocks(T) * 2 * C * 4);
+    s->s_cs_h[i] = take((size_t)ln_bwd_blocks(T) * 3 * C * 4);
+    s->s_cs_x[i] = take((size_t)ln_bwd_blocks(T) * 3 * C * 4);
+    s->s_cs_e[i] = take((size_t)ln_bwd_blocks(T) * 3 * C * 4);
   }
   s->s_zero = take(256);
   // per-microbatch rows
@@ -557,26 +557,16 @@ pulse_status col_sum(pulse_tstage* s, const void* v, int N, float* acc, float* p
   return PULSE_OK;
 }
 
-// acc[n] += sum of rows [0, rows) of partials laid out [rows][2][N] (row 0)
-pulse_status totals(const float* part, int rows, int N, float* acc, hipStream_t st) {
-  RedGrid rg{};
-  rg.chunks = rows;
-  THIP(launch_chan_totals(part, Geo{1, 1, 1}, rg, N, 1, acc, nullptr, nullptr, st));
-  return PULSE_OK;
-}
+// LayerNorm parameter gradients (and a bias gradient, offset < 0: none) from
+// the column-sum partials of a LayerNorm backward
+struct LnSums {
+  const float* part = nullptr;
+  int64_t g = -1, b = -1, bias = -1;
+};
 
-// LayerNorm backward: dx = add + dLN(dy); g/b gradients accumulated; csum
-// (or null) receives the column-sum partials of dx
-pulse_status ln_backward(pulse_tstage* s, const void* dy, const void* x, const float* stats,
-                         int64_t goff, int64_t boff, const void* add, void* dx,
-                         hipStream_t st, float* csum = nullptr) {
-  const int nb = ln_bwd_blocks(s->T);
-  float* part = s->fat(s->s_red);
-  THIP(launch_ln_bwd(dy, x, stats, s->pp(goff), add, s->T, s->C, dx, part, csum, st));
-  RedGrid rg{};
-  rg.chunks = nb;
-  THIP(launch_chan_totals(part, Geo{1, 1, 1}, rg, s->C, 2, s->gp(goff), nullptr, s->gp(boff),
-                          st));
+pulse_status ln_totals(pulse_tstage* s, const LnSums& n, hipStream_t st) {
+  THIP(launch_ln_totals(n.part, ln_bwd_blocks(s->T), s->C, s->gp(n.g), s->gp(n.b),
+                        n.bias >= 0 ? s->gp(n.bias) : nullptr, st));
   return PULSE_OK;
 }
 
@@ -624,6 +614,7 @@ struct BwdSync {
   float* red;         // their reduction buffer
   bool on_side;
   hipEvent_t last = nullptr;  // the side stream's latest recorded event
+  LnSums pending;             // LayerNorm sums for the next fork
 };
 
 hipEvent_t sync_event(pulse_tstage* s) {
@@ -691,13 +682,17 @@ pulse_status wait_for(BwdSync& y, hipEvent_t e) {
 pulse_status join(BwdSync& y) { return wait_for(y, y.last); }
 
 // parameter gradients of one linear layer: bias += colsum(gy), W += gy^T in;
-// with `part` the column sums come from the producer of gy as partials
-// [rows][2][M]
+// with `ln` the bias gradient (if any) and a LayerNorm's parameter gradients
+// come from the LayerNorm backward that produced gy
 pulse_status param_grads(BwdSync& y, int M, const Seg& in, const void* gy, float* bias,
-                         const float* part = nullptr, int rows = 0) {
+                         const LnSums* ln = nullptr) {
   TCHK(fork(y));
-  if (part)
-    TCHK(totals(part, rows, M, bias, y.work));
+  if (y.pending.part) {
+    TCHK(ln_totals(y.s, y.pending, y.work));
+    y.pending = LnSums();
+  }
+  if (ln)
+    TCHK(ln_totals(y.s, *ln, y.work));
   else
     TCHK(col_sum(y.s, gy, M, bias, y.red, y.work));
   TCHK(linear_wgrad(y.s, M, in, gy, y.work));
@@ -705,8 +700,9 @@ pulse_status param_grads(BwdSync& y, int M, const Seg& in, const void* gy, float
 }
 
 // dx = d(block)/dx^T dy for the block input x; parameter gradients +=
+// ln1 receives LN1's column-sum partials
 pulse_status block_bwd(BwdSync& y, SideReads& rd, int par, char* row, const TBlock& b,
-                       const void* x, const void* dy, void* dx, float* dx_csum = nullptr) {
+                       const void* x, const void* dy, void* dx, float* ln1) {
   pulse_tstage* s = y.s;
   hipStream_t st = y.st;
   const int C = s->C, R = s->R;
@@ -739,10 +735,10 @@ pulse_status block_bwd(BwdSync& y, SideReads& rd, int par, char* row, const TBlo
               DT_BF16, st));
   TCHK(wait_for(y, rd.dh));
   float* cs_h = s->fat(s->s_cs_h[par]);
-  TCHK(ln_backward(s, da2, h, st2, b.ln2g, b.ln2b, dy, dh, st, cs_h));
+  THIP(launch_ln_bwd(da2, h, st2, s->pp(b.ln2g), dy, T, C, dh, cs_h, st));
+  const LnSums ln2{cs_h, b.ln2g, b.ln2b, b.projb};
   // attention: h = x + Proj(MHA(LN1(x)))
-  TCHK(param_grads(y, C, tseg(C, tvin(o, C), s->gp(b.projW)), dh, s->gp(b.projb), cs_h,
-                   ln_bwd_blocks(T)));
+  TCHK(param_grads(y, C, tseg(C, tvin(o, C), s->gp(b.projW)), dh, nullptr, &ln2));
   TCHK(mark(y, &rd.dh));
   TCHK(linear(s, C, tseg(C, tvin(dh, C)), s->at(b.t_proj), C, nullptr, nullptr, dO, nullptr,
               DT_BF16, st));
@@ -753,7 +749,7 @@ pulse_status block_bwd(BwdSync& y, SideReads& rd, int par, char* row, const TBlo
   TCHK(mark(y, &rd.dqkv));
   TCHK(linear(s, C, tseg(3 * C, tvin(dqkv, 3 * C)), s->at(b.t_qkv), 3 * C, nullptr, nullptr, da,
               nullptr, DT_BF16, st));
-  TCHK(ln_backward(s, da, x, st1, b.ln1g, b.ln1b, dh, dx, st, dx_csum));
+  THIP(launch_ln_bwd(da, x, st1, s->pp(b.ln1g), dh, T, C, dx, ln1, st));
   return PULSE_OK;
 }
 
@@ -1014,8 +1010,9 @@ pulse_status pulse_tstage_backward(pulse_tstage* s, pulse_half half, int32_t mb,
         // skip linear over [v || skip]
         const int slot = ne - 1 - k;
         const void* skip = row + s->row_slot[slot];
+        const LnSums ln1{cs_x, b.ln1g, b.ln1b, b.skb};
         TCHK(param_grads(y, C, tseg(2 * C, tvin2(row + b.r_v, C, skip, C), s->gp(b.skW)), dsx,
-                         s->gp(b.skb), cs_x, ln_bwd_blocks(s->T)));
+                         nullptr, &ln1));
         TCHK(mark(y, &rd.dsx));
         void* dv = k == 0 ? din : s->at(s->s_dy[k & 1]);
         // dv's buffer held the dy of block k + 1, which the side stream reads
@@ -1043,7 +1040,15 @@ pulse_status pulse_tstage_backward(pulse_tstage* s, pulse_half half, int32_t mb,
                              dy, DT_BF16, T * C, st));
         const void* x = k == 0 ? row + b.r_x : row + s->row_slot[k - 1];
         void* dx = k == 0 ? din : s->at(s->s_dy[1]);
-        TCHK(block_bwd(y, rd, k & 1, row, b, x, dy, dx));
+        // LN1's sums go with the next block's first parameter gradients, whose
+        // event (rd.dy) this stream waits for before that buffer's next use
+        float* cs_e = s->fat(s->s_cs_e[k & 1]);
+        TCHK(block_bwd(y, rd, k & 1, row, b, x, dy, dx, cs_e));
+        const LnSums ln1{cs_e, b.ln1g, b.ln1b, -1};
+        if (k > 0)
+          y.pending = ln1;
+        else
+          TCHK(ln_totals(s, ln1, st));
         g = dx;
       }
     }
