@@ -179,9 +179,12 @@ struct CfgW {
   static constexpr int RA = F32 ? 2 : best_rot(PA), RB = F32 ? 2 : best_rot(PB);
   static constexpr int RA_A = RA % 256, RA_B = RA / 256, RB_A = RB % 256, RB_B = RB / 256;
   static constexpr int LDC = BN + 4;
-  static constexpr int LDS_BYTES = 2 * STAGE;
+  // bias-gradient sums: one per (wave column, tile row)
+  static constexpr int BIAS_BYTES = WAVES_N * BM * 4;
+  static constexpr int LDS_BYTES = 2 * STAGE + BIAS_BYTES;
+  static_assert(WAVES_N == 2, "one wave column per half of a K-step for the bias sums");
   static_assert(16 * LDC * 4 <= STAGE, "epilogue slice must fit one stage");
-  static_assert(2 * STAGE <= 160 * 1024, "LDS");
+  static_assert(LDS_BYTES <= 160 * 1024, "LDS");
   static_assert(WL % NW == 0 && WLA % NW == 0 && (BK * PA) % 1024 == 0 &&
                     (BK * PB) % 1024 == 0,
                 "loads");
@@ -256,6 +259,26 @@ __device__ __forceinline__ v4s ds_rdtr(uint32_t addr) {
   v4s v;
   asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "i"(OFF));
   return v;
+}
+
+// LDS float at addr + OFF += the sum of v over the four 16-lane groups (added
+// by the first one; a wave's LDS operations run in order, so nothing waits
+// for it)
+template <int OFF>
+__device__ __forceinline__ void ds_add(uint32_t addr, float v) {
+  v += __shfl_xor(v, 16, 64);
+  v += __shfl_xor(v, 32, 64);
+  if (__lane_id() < 16)
+    asm volatile("ds_add_f32 %0, %1 offset:%2" ::"v"(addr), "v"(v), "i"(OFF) : "memory");
+}
+
+__device__ __forceinline__ float sum8(bf16x8_t v) {
+  const uint4 w = __builtin_bit_cast(uint4, v);
+  float s = (__uint_as_float(w.x << 16) + __uint_as_float(w.x & 0xffff0000u)) +
+            (__uint_as_float(w.y << 16) + __uint_as_float(w.y & 0xffff0000u));
+  s += (__uint_as_float(w.z << 16) + __uint_as_float(w.z & 0xffff0000u)) +
+       (__uint_as_float(w.w << 16) + __uint_as_float(w.w & 0xffff0000u));
+  return s;
 }
 
 // 16-byte chunk slot of logical chunk lc in row r of a rotated tile (C
@@ -863,10 +886,11 @@ __device__ __forceinline__ void rd_f32x16(float (&v)[16], uint32_t a0, uint32_t 
 // hold as they are, so there is nothing to transpose.  Bound by the fp32 MFMA
 // rate (32 cycles each): a wave of 32 x 32 issues 16 MFMAs per 16 reads, and
 // the other waves of the SIMD cover the reads' wait.
-template <class C, class Issue>
+template <class C, bool BIAS, class Issue>
 __device__ __forceinline__ void wgrad_loop_f32(uint32_t sbase, char* smem, int KT, int wm, int wn,
                                                int lane, Issue& issue,
-                                               f32x4_t (&acc)[C::TM][C::TN]) {
+                                               f32x4_t (&acc)[C::TM][C::TN], int kb, int kbstep,
+                                               uint32_t bslot) {
   static_assert(C::TM == 2 && C::TN == 2, "32 x 32 wave tiles");
   const int g4 = lane >> 4, r16 = lane & 15;
   uint32_t ra[2], rb[2];
@@ -881,7 +905,7 @@ __device__ __forceinline__ void wgrad_loop_f32(uint32_t sbase, char* smem, int K
   float v[2][16];
   // quarter q's 16 MFMAs once its values have landed, with quarter q + 1's
   // reads (all 16 pixels further on) issued before them
-  auto quarter = [&](uint32_t sb, auto q_tag) __attribute__((always_inline)) {
+  auto quarter = [&](uint32_t sb, bool sum, auto q_tag) __attribute__((always_inline)) {
     constexpr int Q = decltype(q_tag)::value;
     float(&x)[16] = v[Q & 1];
     lgkm_wait<0>();
@@ -898,6 +922,10 @@ __device__ __forceinline__ void wgrad_loop_f32(uint32_t sbase, char* smem, int K
         for (int j = 0; j < 2; ++j)
           acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[4 * s + i], x[4 * s + 2 + j],
                                                            acc[i][j], 0, 0, 0);
+    if (sum && wn == (Q >> 1)) {
+      ds_add<0>(bslot, (x[0] + x[4]) + (x[8] + x[12]));
+      ds_add<64>(bslot, (x[1] + x[5]) + (x[9] + x[13]));
+    }
     __builtin_amdgcn_sched_barrier(0);
   };
   if (KT > 0) issue(0, smem);
@@ -907,21 +935,25 @@ __device__ __forceinline__ void wgrad_loop_f32(uint32_t sbase, char* smem, int K
     const uint32_t sb = sbase + (uint32_t)((kt & 1) * C::STAGE);
     rd_f32x16<C, 0>(v[0], sb + ra[0], sb + ra[1], sb + rb[0], sb + rb[1]);
     if (kt + 1 < KT) issue(kt + 1, smem + ((kt + 1) & 1) * C::STAGE);
-    quarter(sb, std::integral_constant<int, 0>());
-    quarter(sb, std::integral_constant<int, 1>());
-    quarter(sb, std::integral_constant<int, 2>());
-    quarter(sb, std::integral_constant<int, 3>());
+    const bool sum = BIAS && kt == kb;
+    if (sum) kb += kbstep;
+    quarter(sb, sum, std::integral_constant<int, 0>());
+    quarter(sb, sum, std::integral_constant<int, 1>());
+    quarter(sb, sum, std::integral_constant<int, 2>());
+    quarter(sb, sum, std::integral_constant<int, 3>());
   }
 }
 
 }  // namespace
 #endif
 
-template <class C>
+// BIAS: the instance that also sums dY's columns (a.bias_part); the other
+// pays neither its LDS nor its test per K-step (1-1.5 %).
+template <class C, bool BIAS>
 __global__ __launch_bounds__(C::NT) void igemm2_wgrad(GemmArgs a, const void* zero16) {
   // the body exists for the device pass only (the host pass emits the launch stub)
 #if defined(__HIP_DEVICE_COMPILE__)
-  __shared__ __attribute__((aligned(1024))) char smem[2 * C::STAGE];
+  __shared__ __attribute__((aligned(1024))) char smem[2 * C::STAGE + (BIAS ? C::BIAS_BYTES : 0)];
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: scalar registers
@@ -942,7 +974,22 @@ __global__ __launch_bounds__(C::NT) void igemm2_wgrad(GemmArgs a, const void* ze
   const long pend = (pbeg + a.kchunk < P) ? pbeg + a.kchunk : P;
   const int tmi = (int)div_rcp((uint32_t)tile, (uint32_t)tilesN, a.rcp_tn);
   const int m0 = tmi * C::BM;
-  const int n0 = (tile - tmi * tilesN) * C::BN;
+  const int tni = tile - tmi * tilesN;
+  const int n0 = tni * C::BN;
+
+  // Bias gradient: the column sums of dY, which the tile rows hold anyway.
+  // The tiles of one row of tiles share its K-steps out (K-step kt belongs to
+  // tile kt % tilesN, one half of it to each wave column), so that no block
+  // does more than its part.  They are kept in LDS, not in registers: two
+  // waves of 208 registers per SIMD are what the other stream's kernels find
+  // room beside.
+  const uint32_t bslot =
+      lds_u32(smem + 2 * C::STAGE) +
+      (uint32_t)((wn * C::BM + wm * C::WM + (lane & 15)) * 4);
+  float* const bias_sm = reinterpret_cast<float*>(smem + 2 * C::STAGE);
+  if (BIAS && lane < 16)
+#pragma unroll
+    for (int i = 0; i < C::TM; ++i) bias_sm[wn * C::BM + wm * C::WM + i * 16 + lane] = 0.f;
 
   const __amdgpu_buffer_rsrc_t rg = make_rsrc(a.gy.s0.ptr, P * a.gy.s0.C * C::ESZ);
   const uint32_t gpitch = (uint32_t)(a.gy.s0.C * C::ESZ);
@@ -1047,7 +1094,7 @@ __global__ __launch_bounds__(C::NT) void igemm2_wgrad(GemmArgs a, const void* ze
   const uint32_t sbase = lds_u32(smem);
   const int KT = (int)((pend - pbeg + C::BK - 1) / C::BK);
   if constexpr (C::F32) {
-    wgrad_loop_f32<C>(sbase, smem, KT, wm, wn, lane, issue, acc);
+    wgrad_loop_f32<C, BIAS>(sbase, smem, KT, wm, wn, lane, issue, acc, BIAS ? tni : KT, tilesN, bslot);
   } else {
   // Transpose reads: lane (g16, j16) addresses pixel row
   // trow = 8 g16 + j16 / 4 (+ 32 s + 4 h) and channel 4 (j16 % 4) of a
@@ -1104,6 +1151,14 @@ __global__ __launch_bounds__(C::NT) void igemm2_wgrad(GemmArgs a, const void* ze
   // Per K-step: wait for the stage, barrier, read the first 32 pixels'
   // fragments, start the next stage's DMA, then the second half's reads
   // overlap the first half's MFMAs.
+  auto add_bias = [&](bf16x8_t (&fa)[C::TM], auto i_tag, auto& self) __attribute__((always_inline)) {
+    constexpr int I = decltype(i_tag)::value;
+    if constexpr (I < C::TM) {
+      ds_add<I * 64>(bslot, sum8(fa[I]));
+      self(fa, std::integral_constant<int, I + 1>(), self);
+    }
+  };
+  int kb = tni;  // the next K-step of this tile's share
   if (KT > 0) issue(0, smem);
   for (int kt = 0; kt < KT; ++kt) {
     wait_vmcnt<0>();
@@ -1118,10 +1173,23 @@ __global__ __launch_bounds__(C::NT) void igemm2_wgrad(GemmArgs a, const void* ze
     __builtin_amdgcn_sched_barrier(0);
     lgkm_wait<0>();
     mma(af[1], bfr[1]);
+    if (BIAS && kt == kb) {
+      kb += tilesN;
+      if (wn == 0)
+        add_bias(af[0], std::integral_constant<int, 0>(), add_bias);
+      else
+        add_bias(af[1], std::integral_constant<int, 0>(), add_bias);
+    }
     __builtin_amdgcn_sched_barrier(0);
   }
   }
+  if constexpr (BIAS) lgkm_wait<0>();  // the sums' LDS adds, which the compiler does not see
   __syncthreads();
+  if constexpr (BIAS) {  // this block's share, the two wave columns
+    float* dst = a.bias_part + ((long)z * tilesN + tni) * a.M + m0;
+    for (int e = tid; e < C::BM && m0 + e < a.M; e += C::NT)
+      dst[e] = bias_sm[e] + bias_sm[C::BM + e];
+  }
 
   // fp32 partials through LDS, GPP wave rows (GPP * WM tile rows) at a
   // time: those waves stage all their accumulators, then every thread
@@ -1248,8 +1316,44 @@ __global__ __launch_bounds__(256) void conv_splitk_finalize(GemmArgs a) {
 // Sum the split partials in split order and accumulate into the gradients
 // of each segment (rows of length end - begin: OHWI for 3x3, [O][I] for 1x1).
 // Four consecutive columns per thread (N and the segment bounds are
-// multiples of 8).
-__global__ void wgrad_finalize(GemmArgs a, int splits) {
+// multiples of 8).  Blocks from wblocks on add the bias gradients: 8 output
+// channels x 32 row lanes each, a lane's rows of bias_part in ascending order
+// (2 loads in flight), the lanes in a fixed tree.  The kernel stays within 16
+// registers: it runs beside the other stream's convs, which leave room for few
+// (with 36, it took 70 us there instead of 40 at 32 x 32 x 640).
+__global__ __launch_bounds__(256) void wgrad_finalize(GemmArgs a, int splits, int wblocks,
+                                                      int brows) {
+  if ((int)blockIdx.x >= wblocks) {
+    __shared__ float sm[32][8];
+    const int tx = threadIdx.x & 7, ty = threadIdx.x >> 3;
+    const int m = ((int)blockIdx.x - wblocks) * 8 + tx;
+    float s = 0.f;
+    constexpr int NB = 2;
+    if (m < a.M) {
+      const float* const bp = a.bias_part;
+      const uint32_t row = 32u * (uint32_t)a.M;  // 32-bit offsets (few registers)
+      uint32_t at = (uint32_t)ty * (uint32_t)a.M + (uint32_t)m;
+#pragma unroll 1
+      for (int i0 = ty; i0 < brows; i0 += NB * 32, at += NB * row) {
+        float v[NB];
+#pragma unroll
+        for (int k = 0; k < NB; ++k) v[k] = i0 + 32 * k < brows ? bp[at + k * row] : 0.f;
+#pragma unroll
+        for (int k = 0; k < NB; ++k) s += v[k];
+      }
+    }
+    sm[ty][tx] = s;
+    __syncthreads();
+    for (int off = 16; off > 0; off >>= 1) {
+      if (ty < off) sm[ty][tx] += sm[ty + off][tx];
+      __syncthreads();
+    }
+    if (ty == 0 && m < a.M) {
+      a.bias_grad[m] += sm[0][tx];
+      if (a.bias_grad2) a.bias_grad2[m] += sm[0][tx];
+    }
+    return;
+  }
   const long idx = ((long)blockIdx.x * blockDim.x + threadIdx.x) * 4;
   if (idx >= (long)a.M * a.N) return;
   const int m = (int)(idx / a.N);
@@ -1372,7 +1476,8 @@ static hipError_t wgrad2_t(const GemmArgs& a_in, int splits, const void* zero16,
     for (int i = 0; i < a.nseg && i < 3; ++i)
       a.rcp_segc[i] = rcp_u32(a.seg[i].C, (long)a.seg[i].taps * a.seg[i].C);
   }
-  hipLaunchKernelGGL(igemm2_wgrad<C>, dim3((unsigned)blocks), dim3(C::NT), 0, st, a, zero16);
+  auto kern = a.bias_part ? igemm2_wgrad<C, true> : igemm2_wgrad<C, false>;
+  hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(C::NT), 0, st, a, zero16);
   return hipGetLastError();
 }
 
@@ -1419,6 +1524,11 @@ hipError_t launch_conv2(const GemmArgs& a, int t, hipStream_t st, hipEvent_t t0,
   return with_conv(t, [&](auto c) { return conv2_t<decltype(c)>(a, st, t0, t1); });
 }
 
+long wgrad_bias_rows(int t, int N, int splits) {
+  const int bn = tile2_info(t).bn;
+  return (long)splits * ((N + bn - 1) / bn);
+}
+
 hipError_t launch_wgrad2(const GemmArgs& a, int t, int splits, const void* zero16,
                          hipStream_t st) {
   hipError_t e;
@@ -1427,10 +1537,13 @@ hipError_t launch_wgrad2(const GemmArgs& a, int t, int splits, const void* zero1
     case TILE2_WF64x64: e = wgrad2_t<W2_F64x64>(a, splits, zero16, st); break;
     default: e = wgrad2_t<W2_128x128>(a, splits, zero16, st); break;
   }
-  if (e != hipSuccess || wgrad_direct(a, splits)) return e;  // added in the epilogue
-  const long total = (long)a.M * a.N / 4;
-  hipLaunchKernelGGL(wgrad_finalize, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, a,
-                     splits);
+  // one split was added in the epilogue: at most the bias gradients remain
+  const bool direct = wgrad_direct(a, splits);
+  if (e != hipSuccess || (direct && !a.bias_part)) return e;
+  const int wblocks = direct ? 0 : (int)(((long)a.M * a.N / 4 + 255) / 256);
+  const int bblocks = a.bias_part ? (a.M + 7) / 8 : 0;
+  hipLaunchKernelGGL(wgrad_finalize, dim3((unsigned)(wblocks + bblocks)), dim3(256), 0, st, a,
+                     splits, wblocks, (int)wgrad_bias_rows(t, a.N, splits));
   return hipGetLastError();
 }
 

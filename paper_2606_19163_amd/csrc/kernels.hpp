@@ -51,6 +51,11 @@ struct GemmArgs {
   VIn gy;              // output gradient, M channels
   int kchunk;          // pixels per split
   float* part;         // [splits][M][N] fp32 partials (both modes)
+  // null, or scratch of wgrad_bias_rows x M floats: the column sums of gy are
+  // added to bias_grad (and bias_grad2, may be null)
+  float* bias_part;
+  float* bias_grad;
+  float* bias_grad2;
   int wdirect;         // set by the wgrad launcher: one pixel split, so the
                        // epilogue adds its tile into the segment gradients
                        // (one writer per element) and no finalize runs
@@ -126,6 +131,7 @@ TileInfo tile2_info(int tile);
 // finalize), which time the launch without marker packets around it.
 hipError_t launch_conv2(const GemmArgs& a, int tile, hipStream_t st, hipEvent_t t0 = nullptr,
                         hipEvent_t t1 = nullptr);
+long wgrad_bias_rows(int tile, int N, int splits);
 hipError_t launch_wgrad2(const GemmArgs& a, int tile, int splits, const void* zero16,
                          hipStream_t st);
 
@@ -190,16 +196,9 @@ hipError_t launch_gn_bwd_apply(const Src& da, const VIn& x, const Geo& g, RedGri
                                int G, const GnBwdOut& o, hipStream_t st,
                                hipEvent_t done = nullptr);
 
-// partial[b][chunk][0][c] = sum over the chunk of v (v may carry an addend).
-hipError_t launch_chan_sum_partial(const VIn& v, const Geo& g, RedGrid rg, float* partial,
-                                   hipStream_t st);
 // pi[s][b][c] = sum_chunk partial[b][chunk][s][c] for s < nslot (pi: [nslot][B][C]).
 hipError_t launch_chan_per_image(const float* partial, const Geo& g, RedGrid rg, int C,
                                  int nslot, float* pi, hipStream_t st);
-// acc0 (and dup) += sum of slot 0, acc1 += sum of slot 1 over every image and
-// chunk, in one pass (no per-image sums)
-hipError_t launch_chan_totals(const float* partial, const Geo& g, RedGrid rg, int C, int nslot,
-                              float* acc0, float* dup, float* acc1, hipStream_t st);
 
 // ---- timestep embedding, weights, copies (misc.hip) ----------------------
 

@@ -483,13 +483,6 @@ __device__ __forceinline__ void chan_totals_block(const float* partial, int rows
   }
 }
 
-__global__ __launch_bounds__(256, GN_WAVES) void k_chan_totals(const float* partial, int rows, int C,
-                                                     int nslot, float* acc0, float* dup,
-                                                     float* acc1) {
-  __shared__ float sm[2][TY][TX];
-  chan_totals_block(partial, rows, C, nslot, blockIdx.x, acc0, dup, acc1, sm);
-}
-
 // GroupNorm backward finalize in one launch of 256-thread blocks: blocks
 // [0, B*G) each reduce one (image, group) to coef = (sum gamma*dz,
 // sum gamma*dz*xhat) / count in fp64, with every load in flight before the
@@ -646,33 +639,6 @@ __global__ __launch_bounds__(256, GN_WAVES) void k_gn_bwd_apply(Src da, VIn x, G
     float* base = o.chan_partial + ((long)r.b * rg.chunks + blockIdx.y) * 2 * C;
     lane_reduce_store<8>(acc, sm, rg, C, base, nullptr);
   }
-}
-
-template <int DT, bool ADD>
-__global__ __launch_bounds__(256) void k_chan_sum_partial(VIn v, Geo g, RedGrid rg,
-                                                          float* partial) {
-  __shared__ float sm[256 * 8];
-  const Range r = block_range(g, rg, v.C);
-  float acc[8];
-#pragma unroll
-  for (int i = 0; i < 8; ++i) acc[i] = 0.f;
-  if (r.active) {
-    const VCh8 h = resolve_v(v, r.c);
-    const long img0 = (long)r.b * g.hw();
-    for (int p = r.p0 + threadIdx.y; p < r.p1; p += U_STATS * rg.py) {
-      long pix[U_STATS];
-      float w[U_STATS], f[U_STATS][8];
-      step_pixels<U_STATS>(p, rg.py, r.p1, img0, pix, w);
-#pragma unroll
-      for (int u = 0; u < U_STATS; ++u) rdv8<DT, ADD>(h, pix[u], f[u]);
-#pragma unroll
-      for (int u = 0; u < U_STATS; ++u)
-#pragma unroll
-        for (int j = 0; j < 8; ++j) acc[j] += w[u] * f[u][j];
-    }
-  }
-  float* base = partial + ((long)r.b * rg.chunks + blockIdx.y) * 2 * v.C;
-  lane_reduce_store<8>(acc, sm, rg, v.C, base, nullptr);
 }
 
 // K-split conv finalize with the statistics of its output, on the grid of
@@ -853,13 +819,6 @@ hipError_t launch_gn_bwd_finalize(const float* partial, const Geo& g, RedGrid rg
   return hipGetLastError();
 }
 
-hipError_t launch_chan_totals(const float* partial, const Geo& g, RedGrid rg, int C, int nslot,
-                              float* acc0, float* dup, float* acc1, hipStream_t st) {
-  hipLaunchKernelGGL(k_chan_totals, dim3((C + TX - 1) / TX), dim3(256), 0, st, partial,
-                     g.B * rg.chunks, C, nslot, acc0, dup, acc1);
-  return hipGetLastError();
-}
-
 namespace {
 
 template <int DT, bool CHAN, bool ADD0>
@@ -896,19 +855,6 @@ hipError_t launch_gn_bwd_apply(const Src& da, const VIn& x, const Geo& g, RedGri
   else
     hipLaunchKernelGGL(kern, red_dims(g, rg, x.C), red_block(rg), 0, st, da, x, g, rg, scale,
                        shift, mean, rstd, gamma, coef, G, o);
-  return hipGetLastError();
-}
-
-hipError_t launch_chan_sum_partial(const VIn& v, const Geo& g, RedGrid rg, float* partial,
-                                   hipStream_t st) {
-  const int dt = common_dt(v);
-  if (dt < 0) return hipErrorInvalidValue;
-  const bool add = v.add != nullptr;
-  auto kern = dt == DT_BF16 ? (add ? k_chan_sum_partial<DT_BF16, true>
-                                   : k_chan_sum_partial<DT_BF16, false>)
-                            : (add ? k_chan_sum_partial<DT_F32, true>
-                                   : k_chan_sum_partial<DT_F32, false>);
-  hipLaunchKernelGGL(kern, red_dims(g, rg, v.C), red_block(rg), 0, st, v, g, rg, partial);
   return hipGetLastError();
 }
 

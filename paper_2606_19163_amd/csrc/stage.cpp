@@ -138,7 +138,9 @@ struct pulse_stage {
          s_pi = 0, s_e = 0, s_zero = 0;
   size_t part_cap = 0;   // weight-gradient split partials (elements)
   size_t kpart_cap = 0;  // conv K-split partials (elements)
-  size_t s_kpart = 0, s_red2 = 0;
+  size_t s_kpart = 0;
+  size_t bpart_cap = 0, s_bpart = 0;  // bias-gradient sums of a weight gradient (elements)
+ 
   size_t s_chp[2] = {0, 0};  // per-chunk channel sums of dh1 (GN2 backward), by block parity
   int cmax = 0;              // widest channel count of any block
   size_t red_cap = 0;        // floats in each reduction buffer
@@ -515,11 +517,13 @@ pulse_status build_layout(pulse_stage* s) {
   s->s_dh1[1] = sc; sc += fbig;
   s->s_g[0] = sc; sc += fbig;
   s->s_g[1] = sc; sc += fbig;
-  size_t part = 0, kpart = 0, red = 0;
+  size_t part = 0, kpart = 0, red = 0, bpart = 0;
   for (auto* v : {&s->eb, &s->db})
     for (auto& b : *v) {
       int sp = wgrad_plan(s, wgrad_tile(s, b.cout, b.ldb2), b.cout, b.ldb2).slots;
       part = std::max(part, (size_t)sp * b.cout * b.ldb2);
+      bpart = std::max(bpart, (size_t)wgrad_bias_rows(wgrad_tile(s, b.cout, b.ldb2), b.ldb2, sp) *
+                                  b.cout);
       sp = wgrad_plan(s, wgrad_tile(s, b.cout, 9 * b.cin), b.cout, 9 * b.cin).slots;
       part = std::max(part, (size_t)sp * b.cout * 9 * b.cin);
       for (int c : {b.cin, b.cout}) {
@@ -531,7 +535,8 @@ pulse_status build_layout(pulse_stage* s) {
   s->s_part = sc; sc += align256(part * 4);
   s->red_cap = red;
   s->s_red = sc; sc += align256(red * 4);
-  s->s_red2 = sc; sc += align256(red * 4);  // reductions on the side stream
+  s->bpart_cap = bpart;
+  s->s_bpart = sc; sc += align256(bpart * 4);
   for (int i = 0; i < 2; ++i) {
     s->s_chp[i] = sc;
     sc += align256(red * 4);
@@ -917,8 +922,9 @@ pulse_status conv_fwd(pulse_stage* s, int N, std::initializer_list<Seg> segs, co
   return run_conv(s, a, st, fwd, stats_chunks);
 }
 
+// bias (null: none), bias2 (null: none) += the column sums of gy
 pulse_status wgrad(pulse_stage* s, int M, std::initializer_list<Seg> segs, const VIn& gy,
-                   hipStream_t st) {
+                   hipStream_t st, float* bias = nullptr, float* bias2 = nullptr) {
   GemmArgs a = gemm_base(s);
   a.M = M;
   int n = 0;
@@ -936,6 +942,13 @@ pulse_status wgrad(pulse_stage* s, int M, std::initializer_list<Seg> segs, const
     return fail(PULSE_E_SHAPE, "internal: wgrad partial buffer too small");
   a.kchunk = w.kchunk;
   a.part = s->sf(s->s_part);
+  if (bias) {
+    if ((size_t)wgrad_bias_rows(tile, n, splits) * M > s->bpart_cap)
+      return fail(PULSE_E_SHAPE, "internal: bias partial buffer too small");
+    a.bias_part = s->sf(s->s_bpart);
+    a.bias_grad = bias;
+    a.bias_grad2 = bias2;
+  }
   HIPCHK(launch_wgrad2(a, tile, splits, s->scratch(s->s_zero), st));
   return PULSE_OK;
 }
@@ -1178,46 +1191,35 @@ pulse_status block_backward(pulse_stage* s, int r, const Block& b, const VIn& xi
   // while the data-gradient chain continues here.  The side stream has its
   // own reduction buffer and weight-gradient partials.
   hipStream_t sd = use_side(s) ? s->side : st;
-  // The shortcut's data gradient (a 1x1 conv over dout: short K, its output
-  // twice dout's width) runs first and alone when this stage's convs fill
-  // the GPU without a K split: beside the weight GEMMs, whose blocks leave no
-  // room for its own on their CUs, it took three times as long.  Where the
-  // convs split K the weight GEMMs bound the backward, and it stays beside
-  // them, after the fork.
+  // The shortcut's data gradient (a 1x1 conv over dout: short K) runs first
+  // and alone: the weight GEMM's blocks leave no room for its own on their
+  // CUs, so beside that GEMM it takes three times as long (64 x 64 x 320: 110
+  // us against 37, 32 x 32 x 640: 106 against 29; 16 x 16 x 1280 iteration
+  // 5840 us against 5650).
   void* dxs = s->scratch(s->s_dxs);
-  auto shortcut_dgrad = [&]() -> pulse_status {
-    return conv_fwd(s, b.cin, {seg1(0, b.cout, dout)}, s->ws + b.wsd, b.cout, nullptr, nullptr,
-                    vnone(), dxs, nullptr, dt, st);
-  };
-  const bool sc_first =
-      b.conv_sc && conv_tiles(s, conv_tile(s, b.cout), b.cout) >= conv_want(s);
-  if (sc_first) {
-    if ((ps = shortcut_dgrad()) != PULSE_OK) return ps;
+  if (b.conv_sc) {
+    if ((ps = conv_fwd(s, b.cin, {seg1(0, b.cout, dout)}, s->ws + b.wsd, b.cout, nullptr, nullptr,
+                       vnone(), dxs, nullptr, dt, st)) != PULSE_OK)
+      return ps;
     s->fork_attached = false;  // the fork below orders the side stream after it
   }
   if ((ps = fork_side(s, st)) != PULSE_OK) return ps;
-  {
-    const RedGrid rg = red_grid(s->geo, b.cout);
-    float* red = s->sf(use_side(s) ? s->s_red2 : s->s_red);
-    HIPCHK(launch_chan_sum_partial(dout, s->geo, rg, red, sd));
-    HIPCHK(launch_chan_totals(red, s->geo, rg, b.cout, 1, s->gp(b.b2),
-                              b.conv_sc ? s->gp(b.bs) : nullptr, nullptr, sd));
-  }
   const VIn a2v = vin1(row + b.a2, dt, b.cout);
   if (b.conv_sc) {
     if ((ps = wgrad(s, b.cout,
                     {seg3(0, b.cout, a2v, s->gp(b.W2)), seg1(9 * b.cout, b.cin, xin, s->gp(b.Ws))},
-                    dout, sd)) != PULSE_OK)
+                    dout, sd, s->gp(b.b2), s->gp(b.bs))) != PULSE_OK)
       return ps;
   } else {
-    if ((ps = wgrad(s, b.cout, {seg3(0, b.cout, a2v, s->gp(b.W2))}, dout, sd)) != PULSE_OK)
+    if ((ps = wgrad(s, b.cout, {seg3(0, b.cout, a2v, s->gp(b.W2))}, dout, sd, s->gp(b.b2),
+                    nullptr)) != PULSE_OK)
       return ps;
   }
   if ((ps = mark_side(s, s->ev_w2[par])) != PULSE_OK) return ps;
   sy.w2[par] = true;
-  // data gradients through conv2 and the shortcut
-  // data gradients are stored in the stage dtype (the MFMA operands they feed
-  // are rounded to it anyway; the GroupNorm backward reads them once more)
+  // The data gradient through conv2.  Data gradients are stored in the stage
+  // dtype (the MFMA operands they feed are rounded to it anyway; the GroupNorm
+  // backward reads them once more).
   void* da = s->scratch(s->s_da);
   // the GroupNorm-backward sums of GN2 (input h1) come from this conv's
   // epilogue when it can produce them (gn2_chunks > 0)
@@ -1232,8 +1234,6 @@ pulse_status block_backward(pulse_stage* s, int r, const Block& b, const VIn& xi
                      nullptr, vnone(), da, nullptr, dt, st, nullptr, &gn2_chunks, &gnb2)) !=
       PULSE_OK)
     return ps;
-  if (b.conv_sc && !sc_first)
-    if ((ps = shortcut_dgrad()) != PULSE_OK) return ps;
   // GN2 backward -> dh1, with per-image channel sums (the temb gradient);
   // dh1 alternates between two buffers: the one written here was last read
   // by the conv1 weight gradient of the block before the previous one

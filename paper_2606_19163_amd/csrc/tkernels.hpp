@@ -32,10 +32,10 @@ hipError_t launch_attn_bwd(const void* qkv, const void* o, const void* dout, con
 // y = LN(x) * g + b per token; stats[2 t] = mean, stats[2 t + 1] = rstd.
 hipError_t launch_ln_fwd(const void* x, long T, int C, float eps, const float* g, const float* b,
                          void* y, float* stats, hipStream_t st);
-// dx = add + d LN / dx (add [T][C] bf16 or null); part[ln_bwd_blocks(T)][3][C]
+// dx = add + d LN / dx (add [T][C] bf16 or null); part[ln_bwd_blocks(T, C)][3][C]
 // receives per-block column sums of dy * xhat, dy and dx as stored.  done
 // (may be null): an event recorded by the kernel's own completion.
-int ln_bwd_blocks(long T);
+int ln_bwd_blocks(long T, int C);
 hipError_t launch_ln_bwd(const void* dy, const void* x, const float* stats, const float* g,
                          const void* add, long T, int C, void* dx, float* part, hipStream_t st,
                          hipEvent_t done = nullptr);

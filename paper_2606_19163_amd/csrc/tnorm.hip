@@ -14,7 +14,7 @@ namespace pulse {
 namespace {
 
 constexpr int LN_VEC = 4;        // 8-channel vectors per lane: C <= 64 * 8 * LN_VEC = 2048
-constexpr int LN_BLOCKS = 512;   // of the backward pass: two per CU
+constexpr int LN_BLOCKS = 512;   // of the backward pass, at most: two per CU
 
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
@@ -88,108 +88,123 @@ __global__ __launch_bounds__(256) void k_ln_fwd(const uint16_t* x, long T, int C
 }
 
 // dx = add + rstd * (dxh - mean(dxh) - xh * mean(dxh * xh)), dxh = dy * g.
-// A wave takes every (4 x blocks)-th token, the next token's rows in flight
-// while the current one is reduced, and keeps its column sums of dy * xh, dy
-// and dx (as stored) in registers over its tokens; the block's four waves
-// meet in LDS and part[block][3][C] receives those sums.  Bound by HBM (three
-// rows read, one written per token).  NV, the 8-channel vectors per lane, is
-// the width's own: with registers for 2048 channels and one token per wave,
-// 4096 tokens of 768 channels wrote as many bytes of partials as of
-// activations and found little room beside the weight GEMMs of the other
-// stream: 34.6 us there on average against 16.5 now (10 us alone; 1408
-// channels, 8192 tokens: 39 -> 31 us alone).
-template <int NV>
-__global__ __launch_bounds__(256) void k_ln_bwd(const uint16_t* dy, const uint16_t* x,
-                                                const float2* stats, const float* g,
-                                                const uint16_t* add, long T, int C, uint16_t* dx,
-                                                float* part) {
-  __shared__ float sm[3][4][64 * 8];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int nv = C / 8;
-  const long step = (long)gridDim.x * 4;
-  float acc[3][NV][8];
+// WR waves hold one token's row, 8 channels per lane, so that a lane's column
+// sums of dy * xh, dy and dx (as stored), kept over the tokens of its row
+// group, take 24 registers whatever the width: the kernel stays within the 96
+// that a weight-gradient GEMM of the other stream (two waves of 208 per SIMD)
+// leaves, instead of waiting for its blocks to end.  A block holds RG row
+// groups; the next token's rows are in flight while the current one is
+// reduced (wave shuffles, then the WR waves through LDS, one barrier per
+// token).  part[block][3][C] receives the block's column sums.  Bound by HBM:
+// three rows read, one written per token.
+template <int WR, int RG>
+__global__ __launch_bounds__(64 * WR * RG, 5) void k_ln_bwd(const uint16_t* dy, const uint16_t* x,
+                                                            const float2* stats, const float* g,
+                                                            const uint16_t* add, int T, int C,
+                                                            uint16_t* dx, float* part) {
+  __shared__ float2 red[2][RG][WR];
+  __shared__ float sm[RG > 1 ? RG * 3 * WR * 512 : 1];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int wr = wave % WR, rg = wave / WR;
+  const int nv = C / 8, vi = wr * 64 + lane;
+  const bool on = vi < nv;
+  const int vc = (on ? vi : nv - 1) * 8;  // lanes past the row reload its end
+  const int step = gridDim.x * RG;
+  float acc[3][8], gv[8];
 #pragma unroll
   for (int r = 0; r < 3; ++r)
 #pragma unroll
-    for (int j = 0; j < NV; ++j)
-#pragma unroll
-      for (int i = 0; i < 8; ++i) acc[r][j][i] = 0.f;
-  uint4 xr[NV], dr[NV], ar[NV];
-  float2 st = make_float2(0.f, 0.f);
-  auto load = [&](long t) __attribute__((always_inline)) {
-    st = stats[t];
-#pragma unroll
-    for (int j = 0; j < NV; ++j) {
-      const int vi = min(lane + 64 * j, nv - 1);  // lanes past the row reload its end
-      xr[j] = *reinterpret_cast<const uint4*>(x + t * C + vi * 8);
-      dr[j] = *reinterpret_cast<const uint4*>(dy + t * C + vi * 8);
-      if (add) ar[j] = *reinterpret_cast<const uint4*>(add + t * C + vi * 8);
-    }
+    for (int i = 0; i < 8; ++i) acc[r][i] = 0.f;
+  {
+    const float4 g0 = reinterpret_cast<const float4*>(g + vc)[0];
+    const float4 g1 = reinterpret_cast<const float4*>(g + vc)[1];
+    gv[0] = g0.x; gv[1] = g0.y; gv[2] = g0.z; gv[3] = g0.w;
+    gv[4] = g1.x; gv[5] = g1.y; gv[6] = g1.z; gv[7] = g1.w;
+  }
+  uint4 xr, dr, ar = {0u, 0u, 0u, 0u};
+  float2 st;
+  // every row group runs the same count of steps (a barrier each); past T
+  // the loads repeat the last token and nothing is stored or summed
+  auto load = [&](int t) __attribute__((always_inline)) {
+    const int tc = t < T ? t : T - 1;
+    const int e = tc * C + vc;  // T * C elements stay below 2^30
+    st = stats[tc];
+    xr = *reinterpret_cast<const uint4*>(x + e);
+    dr = *reinterpret_cast<const uint4*>(dy + e);
+    if (add) ar = *reinterpret_cast<const uint4*>(add + e);
   };
-  long t = (long)blockIdx.x * 4 + w;
-  if (t < T) load(t);
-  for (; t < T; t += step) {
-    float xh[NV][8], gy[NV][8], a[NV][8];
+  int t = blockIdx.x * RG + rg;
+  load(t);
+  int buf = 0;
+#pragma unroll 1
+  for (int tb = blockIdx.x * RG; tb < T; tb += step, t += step, buf ^= 1) {
+    float xh[8], gy[8];
     float s1 = 0.f, s2 = 0.f;
     const float rs = st.y;
+    const bool ok = on && t < T;
+    const uint4 ac = ar;
+    up8bf(xr, xh);
+    up8bf(dr, gy);
 #pragma unroll
-    for (int j = 0; j < NV; ++j) {
-      const int vi = lane + 64 * j;
-      float dv[8];
-      up8bf(xr[j], xh[j]);
-      up8bf(dr[j], dv);
+    for (int i = 0; i < 8; ++i) {
+      xh[i] = (xh[i] - st.x) * rs;
+      const float d = ok ? gy[i] : 0.f;
+      acc[0][i] += d * xh[i];
+      acc[1][i] += d;
+      gy[i] = d * gv[i];
+      s1 += gy[i];
+      s2 += gy[i] * xh[i];
+    }
+    if (tb + step < T) load(t + step);
+    s1 = wave_sum(s1);
+    s2 = wave_sum(s2);
+    if constexpr (WR > 1) {
+      if (lane == 0) red[buf][rg][wr] = make_float2(s1, s2);
+      __syncthreads();
+      s1 = s2 = 0.f;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) a[j][i] = 0.f;
-      if (add) up8bf(ar[j], a[j]);
-      if (vi < nv) {
-        const float4 g0 = reinterpret_cast<const float4*>(g)[2 * vi];
-        const float4 g1 = reinterpret_cast<const float4*>(g)[2 * vi + 1];
-        const float gv[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          xh[j][i] = (xh[j][i] - st.x) * rs;
-          gy[j][i] = dv[i] * gv[i];
-          s1 += gy[j][i];
-          s2 += gy[j][i] * xh[j][i];
-          acc[0][j][i] += dv[i] * xh[j][i];
-          acc[1][j][i] += dv[i];
-        }
+      for (int q = 0; q < WR; ++q) {
+        s1 += red[buf][rg][q].x;
+        s2 += red[buf][rg][q].y;
       }
     }
-    if (t + step < T) load(t + step);
-    const float m1 = wave_sum(s1) / C, m2 = wave_sum(s2) / C;
+    const float m1 = s1 / C, m2 = s2 / C;
+    if (ok) {
+      float o[8];
+      up8bf(ac, o);
 #pragma unroll
-    for (int j = 0; j < NV; ++j) {
-      const int vi = lane + 64 * j;
-      if (vi < nv) {
-        float o[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          o[i] = a[j][i] + rs * (gy[j][i] - m1 - xh[j][i] * m2);
-          acc[2][j][i] += bf2f(f2bf(o[i]));  // the value as stored
-        }
-        st8bf(dx + t * C + vi * 8, o);
+      for (int i = 0; i < 8; ++i) {
+        o[i] += rs * (gy[i] - m1 - xh[i] * m2);
+        acc[2][i] += bf2f(f2bf(o[i]));  // the value as stored
       }
+      st8bf(dx + (t * C + vc), o);
     }
   }
-  // the four waves' column sums, in wave order, one vector slice at a time
   float* out = part + (long)blockIdx.x * 3 * C;
+  if constexpr (RG == 1) {
+    if (on) {
 #pragma unroll
-  for (int j = 0; j < NV; ++j) {
-    if (j) __syncthreads();
+      for (int r = 0; r < 3; ++r) {
+        float4* p = reinterpret_cast<float4*>(out + (long)r * C + vc);
+        p[0] = make_float4(acc[r][0], acc[r][1], acc[r][2], acc[r][3]);
+        p[1] = make_float4(acc[r][4], acc[r][5], acc[r][6], acc[r][7]);
+      }
+    }
+  } else {
+    // the row groups' sums, in group order (element i of lane l at 64 i + l)
 #pragma unroll
     for (int r = 0; r < 3; ++r)
 #pragma unroll
-      for (int i = 0; i < 8; ++i) sm[r][w][lane + 64 * i] = acc[r][j][i];
+      for (int i = 0; i < 8; ++i)
+        sm[((rg * 3 + r) * WR + wr) * 512 + 64 * i + lane] = acc[r][i];
     __syncthreads();
-    for (int e = threadIdx.x; e < 3 * 512; e += 256) {
-      const int r = e >> 9, c = e & 511;  // column c of this slice
-      if (j * 512 + c >= C) continue;
-      const int at = (c >> 3) + 64 * (c & 7);
-      float s = sm[r][0][at];
+    for (int e = threadIdx.x; e < 3 * C; e += 64 * WR * RG) {
+      const int r = e / C, c = e - r * C;
+      const int at = (r * WR + (c >> 9)) * 512 + 64 * (c & 7) + ((c & 511) >> 3);
+      float s = sm[at];
 #pragma unroll
-      for (int ww = 1; ww < 4; ++ww) s += sm[r][ww][at];
-      out[(long)r * C + j * 512 + c] = s;
+      for (int q = 1; q < RG; ++q) s += sm[q * 3 * WR * 512 + at];
+      out[e] = s;
     }
   }
 }
@@ -255,7 +270,15 @@ unsigned grid_of(long n, long cap = 8192) {
 
 }  // namespace
 
-int ln_bwd_blocks(long T) { return (int)std::min<long>((T + 3) / 4, LN_BLOCKS); }
+namespace {
+// waves per row and row groups per block of the backward for C channels
+int ln_wr(int C) { return (C + 511) / 512; }
+int ln_rg(int C) { return ln_wr(C) == 1 ? 4 : ln_wr(C) == 2 ? 2 : 1; }
+}  // namespace
+
+int ln_bwd_blocks(long T, int C) {
+  return (int)std::min<long>((T + ln_rg(C) - 1) / ln_rg(C), LN_BLOCKS);
+}
 
 hipError_t launch_ln_fwd(const void* x, long T, int C, float eps, const float* g, const float* b,
                          void* y, float* stats, hipStream_t st) {
@@ -270,19 +293,19 @@ hipError_t launch_ln_bwd(const void* dy, const void* x, const float* stats, cons
                          const void* add, long T, int C, void* dx, float* part, hipStream_t st,
                          hipEvent_t done) {
   if (C % 8 || C > 64 * 8 * LN_VEC) return hipErrorInvalidValue;
-  auto kern = C <= 512 ? k_ln_bwd<1> : C <= 1024 ? k_ln_bwd<2> : C <= 1536 ? k_ln_bwd<3>
-                                                                            : k_ln_bwd<4>;
-  const dim3 grid((unsigned)ln_bwd_blocks(T)), block(256);
+  auto kern = C <= 512 ? k_ln_bwd<1, 4> : C <= 1024 ? k_ln_bwd<2, 2> : C <= 1536 ? k_ln_bwd<3, 1>
+                                                                                  : k_ln_bwd<4, 1>;
+  const dim3 grid((unsigned)ln_bwd_blocks(T, C)), block(64 * ln_wr(C) * ln_rg(C));
   const uint16_t* d = static_cast<const uint16_t*>(dy);
   const uint16_t* xi = static_cast<const uint16_t*>(x);
   const float2* ss = reinterpret_cast<const float2*>(stats);
   const uint16_t* ad = static_cast<const uint16_t*>(add);
   uint16_t* o = static_cast<uint16_t*>(dx);
   if (done)  // the event completes with the kernel (no marker packet of its own)
-    hipExtLaunchKernelGGL(kern, grid, block, 0, st, nullptr, done, 0, d, xi, ss, g, ad, T, C, o,
+    hipExtLaunchKernelGGL(kern, grid, block, 0, st, nullptr, done, 0, d, xi, ss, g, ad, (int)T, C, o,
                           part);
   else
-    hipLaunchKernelGGL(kern, grid, block, 0, st, d, xi, ss, g, ad, T, C, o, part);
+    hipLaunchKernelGGL(kern, grid, block, 0, st, d, xi, ss, g, ad, (int)T, C, o, part);
   return hipGetLastError();
 }
 

@@ -112,9 +112,8 @@ struct pulse_tstage {
   // previous one left (the side stream rarely lags that far)
   size_t s_dy[2] = {0, 0}, s_dm[2] = {0, 0}, s_da2 = 0, s_dh[2] = {0, 0}, s_do = 0,
          s_dqkv[2] = {0, 0}, s_da = 0, s_dsx[2] = {0, 0}, s_dv = 0, s_dsum = 0, s_kpart = 0,
-         s_wpart = 0, s_red = 0, s_zero = 0;
-  size_t kpart_cap = 0, wpart_cap = 0, red_cap = 0;
-  size_t s_red2 = 0;  // reduction buffer of the side stream
+         s_wpart = 0, s_bpart = 0, s_zero = 0;
+  size_t kpart_cap = 0, wpart_cap = 0, bpart_cap = 0;
   // column-sum partials of the LayerNorm backward, per block parity: LN2's
   // (its gains and dh, the bias gradient of proj), a decoder block's LN1's
   // (its gains and the skip linear's output gradient, whose bias gradient it
@@ -357,7 +356,7 @@ void build_layout(pulse_tstage* s) {
   s->s_dv = take(act);
   s->s_dsum = take(lbytes);
   // partial buffers: the largest conv K split and weight-gradient split
-  size_t kcap = 0, wcap = 0;
+  size_t kcap = 0, wcap = 0, bcap = 0;
   const int gemms[][3] = {{3 * C, C, 0}, {C, C, 0}, {R, C, 0}, {C, R, 0}, {C, 2 * C, 0},
                           {C, 3 * C, 0}, {C, R, 0}, {R, C, 0}};
   for (const auto& g : gemms) {
@@ -368,20 +367,19 @@ void build_layout(pulse_tstage* s) {
     int kc = 0;
     const int sp = twgrad_splits(twgrad_tile(s->wgrad_tile_force, N, T), T, N, K, kc);
     wcap = std::max(wcap, (size_t)sp * N * K);
+    const long rows = wgrad_bias_rows(twgrad_tile(s->wgrad_tile_force, N, T), K, sp);
+    bcap = std::max(bcap, (size_t)rows * N);
   }
   s->kpart_cap = kcap;
   s->wpart_cap = wcap;
   s->s_kpart = take(std::max<size_t>(kcap, 4) * 4);
   s->s_wpart = take(std::max<size_t>(wcap, 4) * 4);
-  // reductions: bias-gradient chunk partials [chunks <= 128][2][N <= max(3C, R)]
-  const size_t red = (size_t)128 * 2 * std::max(3 * C, R);
-  s->red_cap = red;
-  s->s_red = take(red * 4);
-  s->s_red2 = take(red * 4);
+  s->bpart_cap = bcap;
+  s->s_bpart = take(bcap * 4);
   for (int i = 0; i < 2; ++i) {
-    s->s_cs_h[i] = take((size_t)ln_bwd_blocks(T) * 3 * C * 4);
-    s->s_cs_x[i] = take((size_t)ln_bwd_blocks(T) * 3 * C * 4);
-    s->s_cs_e[i] = take((size_t)ln_bwd_blocks(T) * 3 * C * 4);
+    s->s_cs_h[i] = take((size_t)ln_bwd_blocks(T, C) * 3 * C * 4);
+    s->s_cs_x[i] = take((size_t)ln_bwd_blocks(T, C) * 3 * C * 4);
+    s->s_cs_e[i] = take((size_t)ln_bwd_blocks(T, C) * 3 * C * 4);
   }
   s->s_zero = take(256);
   // per-microbatch rows
@@ -524,8 +522,8 @@ pulse_status linear(pulse_tstage* s, int N, const Seg& in, const void* W, int ld
   return PULSE_OK;
 }
 
-// grad[M][in.end] += gy[T][M]^T in[T][K]
-pulse_status linear_wgrad(pulse_tstage* s, int M, const Seg& in, const void* gy,
+// grad[M][in.end] += gy[T][M]^T in[T][K]; bias (null: none) += colsum(gy)
+pulse_status linear_wgrad(pulse_tstage* s, int M, const Seg& in, const void* gy, float* bias,
                           hipStream_t st) {
   GemmArgs a = tbase(s);
   a.M = M;
@@ -541,19 +539,13 @@ pulse_status linear_wgrad(pulse_tstage* s, int M, const Seg& in, const void* gy,
     return tfail(PULSE_E_SHAPE, "internal: weight-gradient partial buffer too small");
   a.kchunk = kc;
   a.part = s->fat(s->s_wpart);
+  if (bias) {
+    if ((size_t)wgrad_bias_rows(wtile, a.N, splits) * M > s->bpart_cap)
+      return tfail(PULSE_E_SHAPE, "internal: bias partial buffer too small");
+    a.bias_part = s->fat(s->s_bpart);
+    a.bias_grad = bias;
+  }
   THIP(launch_wgrad2(a, wtile, splits, s->at(s->s_zero), st));
-  return PULSE_OK;
-}
-
-// acc[n] += sum over the T tokens of v[t][n] (part: a reduction buffer)
-pulse_status col_sum(pulse_tstage* s, const void* v, int N, float* acc, float* part,
-                     hipStream_t st) {
-  const Geo g{1, (int)s->T, 1};
-  const RedGrid rg = red_grid(g, N);
-  if ((size_t)rg.chunks * 2 * N > s->red_cap)
-    return tfail(PULSE_E_SHAPE, "internal: reduction buffer too small");
-  THIP(launch_chan_sum_partial(tvin(v, N), g, rg, part, st));
-  THIP(launch_chan_totals(part, g, rg, N, 1, acc, nullptr, nullptr, st));
   return PULSE_OK;
 }
 
@@ -565,7 +557,7 @@ struct LnSums {
 };
 
 pulse_status ln_totals(pulse_tstage* s, const LnSums& n, hipStream_t st) {
-  THIP(launch_ln_totals(n.part, ln_bwd_blocks(s->T), s->C, s->gp(n.g), s->gp(n.b),
+  THIP(launch_ln_totals(n.part, ln_bwd_blocks(s->T, s->C), s->C, s->gp(n.g), s->gp(n.b),
                         n.bias >= 0 ? s->gp(n.bias) : nullptr, st));
   return PULSE_OK;
 }
@@ -611,7 +603,6 @@ struct BwdSync {
   pulse_tstage* s;
   hipStream_t st;     // the caller's stream
   hipStream_t work;   // where parameter gradients run: side or st
-  float* red;         // their reduction buffer
   bool on_side;
   hipEvent_t last = nullptr;  // the side stream's latest recorded event
   LnSums pending;             // LayerNorm sums for the next fork
@@ -632,7 +623,6 @@ BwdSync bwd_sync(pulse_tstage* s, hipStream_t st, bool keep_events = false) {
   y.st = st;
   y.on_side = s->side != nullptr && !s->timing;
   y.work = y.on_side ? s->side : st;
-  y.red = s->fat(y.on_side ? s->s_red2 : s->s_red);
   if (!keep_events) s->sev_used = 0;
   return y;
 }
@@ -691,11 +681,8 @@ pulse_status param_grads(BwdSync& y, int M, const Seg& in, const void* gy, float
     TCHK(ln_totals(y.s, y.pending, y.work));
     y.pending = LnSums();
   }
-  if (ln)
-    TCHK(ln_totals(y.s, *ln, y.work));
-  else
-    TCHK(col_sum(y.s, gy, M, bias, y.red, y.work));
-  TCHK(linear_wgrad(y.s, M, in, gy, y.work));
+  if (ln) TCHK(ln_totals(y.s, *ln, y.work));
+  TCHK(linear_wgrad(y.s, M, in, gy, bias, y.work));
   return PULSE_OK;
 }
 

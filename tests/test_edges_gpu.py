@@ -74,3 +74,15 @@ def test_small_tiles_forced(monkeypatch, tile, batch, h, w):
     monkeypatch.setenv("PULSE_CONV_TILE", str(tile))
     monkeypatch.setenv("PULSE_CONV_KSPLIT_MAX", "1")
     _parity(_pair(batch, h, w, 128, 32, 64, configs.BF16, 1), 24, f"tile{tile}")
+
+
+# bias gradients inside the weight GEMMs: fewer K-steps than column tiles
+# (8 x 8 images), more, rows past the tile (288 and 448 of 320- and 128-row
+# tiles) and the fp32 loop; their sums go to two biases in decoder blocks
+BIAS = [(configs.BF16, 1, 8, 8, 320), (configs.BF16, 2, 33, 20, 448), (configs.BF16, 1, 20, 33, 288),
+        (configs.F32, 1, 40, 17, 96)]
+
+
+@pytest.mark.parametrize("dtype,batch,h,w,c", BIAS, ids=[f"{d}-{b}x{h}x{w}x{c}" for d, b, h, w, c in BIAS])
+def test_bias_gradients(dtype, batch, h, w, c):
+    _parity(_pair(batch, h, w, c, 32, 64, dtype, 1), 25, f"bias {dtype} {batch}x{h}x{w}x{c}")
