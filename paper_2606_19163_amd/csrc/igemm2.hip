@@ -74,8 +74,9 @@ __device__ __forceinline__ void wait_stages(int after) {
 // fp32 values and a fragment is 16 bytes per lane either way: 8 bf16 k
 // values of one MFMA, or one fp32 k value of each of four.
 template <int BM_, int BN_, int WM_, int WN_, int STAGES_ = 2, int BK_ = 64, bool F32_ = false,
-          int KG_ = 1>
+          int KG_ = 1, bool RF_ = true>
 struct CfgC {
+  static constexpr bool RF = RF_;             // fragment reads before the next stage's DMA
   static constexpr bool F32 = F32_;
   static constexpr int ESZ = F32 ? 4 : 2;     // bytes per element
   static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, BK = BK_, STAGES = STAGES_;
@@ -553,8 +554,9 @@ __global__ __launch_bounds__(C::NT) void igemm2_conv(GemmArgs a) {
 
   // Per K-step: wait for this stage's DMA (the later stages stay in
   // flight), barrier, start the DMA of the stage STAGES-1 ahead into the slot
-  // read one step ago, issue every fragment read of this stage, then the
-  // MFMAs of each K-half once its fragments have landed.
+  // read one step ago and issue every fragment read of this stage (in the
+  // tile's order of the two), then the MFMAs of each K-half once its fragments
+  // have landed.
   bf16x8_t af[C::KH][C::TM], bfr[C::KH][C::TN];
   if (C::KG == 1 || KT > 0) issue(0);
 #pragma unroll
@@ -572,16 +574,20 @@ __global__ __launch_bounds__(C::NT) void igemm2_conv(GemmArgs a) {
     __builtin_amdgcn_s_barrier();
     if (C::KG > 1 && kt >= KT) continue;  // a shorter group keeps the barriers
     const uint32_t sb = sbase + (uint32_t)(slot * C::STAGE);
+    // the slot refilled here was read one step ago: every wave is past that
+    auto refill = [&]() __attribute__((always_inline)) {
+      if (kt + C::STAGES - 1 < KT) {
+        const int ns = slot + C::STAGES - 1;
+        issue((uint32_t)((ns >= C::STAGES ? ns - C::STAGES : ns) * C::STAGE));
+      }
+    };
+    if constexpr (!C::RF) refill();
 #pragma unroll
     for (int s = 0; s < C::KH; ++s) {
       ds_rd_n<C::TM, 16 * C::RB, 0>(af[s], sb + fa[s]);
       ds_rd_n<C::TN, 16 * C::RB, C::A_BYTES>(bfr[s], sb + fb[s]);
     }
-    // the slot refilled here was read one step ago: every wave is past that
-    if (kt + C::STAGES - 1 < KT) {
-      const int ns = slot + C::STAGES - 1;
-      issue((uint32_t)((ns >= C::STAGES ? ns - C::STAGES : ns) * C::STAGE));
-    }
+    if constexpr (C::RF) refill();
     slot = slot + 1 == C::STAGES ? 0 : slot + 1;
 #pragma unroll
     for (int s = 0; s < C::KH; ++s) {
@@ -1376,8 +1382,14 @@ __global__ __launch_bounds__(256) void wgrad_finalize(GemmArgs a, int splits, in
 // ---------------------------------------------------------------------------
 
 namespace launch2 {
-using C2_128x160 = CfgC<128, 160, 64, 80>;   // 4 waves, two blocks per CU
-using C2_128x128 = CfgC<128, 128, 64, 64>;   // 4 waves, two blocks per CU
+// The two tiles of the full-size 3x3 convs start the next stage's DMA before
+// their fragment reads: its latency counts there once more than one round of
+// blocks runs (16 x 48 x 48 x 256 132 us per conv against 142 with the reads
+// first; sampling at 16 x 20 x 20 x 960 1566 against 1664 us, 16 x 19 x 61 x
+// 320 755 against 792, 8 x 64 x 64 x 320 the same).  128 x 192, which only the
+// token GEMMs take, reads first (8192 x 1408 x 5632 124 us against 128).
+using C2_128x160 = CfgC<128, 160, 64, 80, 2, 64, false, 1, false>;  // 4 waves, two blocks per CU
+using C2_128x128 = CfgC<128, 128, 64, 64, 2, 64, false, 1, false>;  // 4 waves, two blocks per CU
 using C2_128x192 = CfgC<128, 192, 64, 96>;   // 4 waves, two blocks per CU
 using C2_64x128S3 = CfgC<64, 128, 32, 64, 3>;  // 4 waves, 3 stages, two blocks per CU
 // grids that do not fill the GPU
