@@ -564,31 +564,74 @@ __global__ __launch_bounds__(256) void k_attn_bwd_kv_s(const uint16_t* qkv, cons
 }
 
 // ---------------------------------------------------------------------------
-// forward, key-split form (any L): block (64-query tile, head, image).  The
-// keys stream through LDS 128 at a time and wave w takes keys 32 w .. + 31
-// of every chunk for all 64 queries, so each K or V fragment read from LDS
-// feeds four MFMAs (one per 16-query block) and p never leaves registers:
-//   s^T = k q^T   A = k rows (LDS), B = q (registers); the output lane
-//                 (g, m) holds keys 8 g + 4 kb + i of query 16 qb + m
-//   o^T += v^T p^T  A = v read down the tile (lane (g, j): keys 8 g + t of
-//                 channel 16 db + j), B = p^T (lane (g, m): keys 8 g + t of
-//                 query m, t = 4 kb + i: exactly the values the lane holds)
-// For the first product to deliver keys 8 g + 4 kb + i on output row 4 g + i
-// of block kb, every 32-key group is stored with its rows permuted: key k at
-// row (k & 3) | ((k >> 3) & 3) << 2 | ((k >> 2) & 1) << 4, so that rows
-// 16 kb .. 16 kb + 15 hold keys 8 (m >> 2) + 4 kb + (m & 3), m = 0..15.
-// Every wave keeps a running maximum and sum per query (online softmax); at
-// the end the four partial states are merged through LDS.
+// Backward for long sequences, with p and ds in registers (attn_bwd_long
+// says when).  The streamed kernels above are bound by LDS: every operand is
+// read once per 16 rows, and p and ds pass through a strip.  Here, as in the
+// key-split forward below, the score products are formed transposed, so that
+// the lane that receives p or ds holds exactly the k index range that the
+// next product's B operand wants of it; each LDS read feeds two or four
+// MFMAs.  Tiles are stored with the rows of every 32-row group permuted
+// (kperm), and one copy serves both the row reads of the score products and
+// the transposed reads after them.  MFMA and VALU (2.5 to 3 instructions per
+// MFMA) bound what is left; 256 registers, two blocks per CU.  Measured, dq
+// and dk + dv kernels (us): 1 x 4096 tokens of 8 heads 108 + 131 -> 70 + 86,
+// 8 x 1024 of 22 157 + 194 -> 143 + 158.
+//
+//   dq tile : 64 queries in every wave's registers, wave w takes keys
+//             32 w .. + 31 of each 128-key chunk
+//             s^T = k q^T, dp^T - D = v do^T - D, dq^T += k^T ds^T
+//   dk, dv  : wave (wk, wq) owns keys 32 wk .. + 31 of the 64-key tile and
+//             takes queries 32 wq .. + 31 of each 64-query chunk
+//             s = q k^T, dp - D = do v^T - D, dv^T += do^T p, dk^T += q^T ds
+//
+// The waves' partial sums meet in LDS once, at the end.  -D enters as the
+// accumulator of dp; the factor 1/8 of ds is a power of two and is applied to
+// the sums.
 // ---------------------------------------------------------------------------
 
-constexpr int KS_CHUNK = 128;  // keys per chunk: 4 waves x 32
+constexpr int KS_CHUNK = 128;  // keys per chunk of the key-split kernels: 4 waves x 32
 constexpr int OPAD = 65;       // floats per row of the merge buffers
 
+// row of key (or query) k in a permuted tile: rows 16 kb .. 16 kb + 15 of a
+// 32-row group hold k = 8 (m >> 2) + 4 kb + (m & 3), m = 0..15
 __device__ __forceinline__ int kperm(int k) {
   return (k & ~31) | (k & 3) | (((k >> 3) & 3) << 2) | (((k >> 2) & 1) << 4);
 }
 
-// Chunk staging of the key-split forward.  Thread t moves 16-byte piece
+// chunk permutation of a permuted tile that is also read down its rows: a
+// transposed read takes rows 8 a .. 8 a + 7 per half wave, so bits 1 and 2 of
+// the row select the 32-byte column pair and bit 3 the chunk within it
+__device__ __forceinline__ int poff(int r, int c) {
+  const int x = (((r >> 1) & 1) << 1) | (((r >> 2) & 1) << 2) | ((r >> 3) & 1);
+  return r * HD + ((c ^ x) << 3);
+}
+
+// as frag_row, in a permuted tile
+__device__ __forceinline__ bf16x8 frag_row_p(const uint16_t* t, int r, int kk, int g) {
+  return *reinterpret_cast<const bf16x8*>(t + poff(r, 4 * kk + g));
+}
+
+// as frag_tr, in a permuted tile: r0 + 8 g .. + 3 sit at rows r0 + 4 g, the
+// next four 16 rows further
+__device__ __forceinline__ bf16x8 frag_tr_p(const uint16_t* t, int r0, int d0, int lane) {
+  const int g = lane >> 4, j = lane & 15;
+  const int col = d0 + 4 * (j & 3);
+  const int r = r0 + 4 * g + (j >> 2);
+  const v4s lo = rd_tr(t + poff(r, col >> 3) + (col & 7));
+  const v4s hi = rd_tr(t + poff(r + 16, col >> 3) + (col & 7));
+  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+// as chunk_store, into a permuted tile
+__device__ __forceinline__ void chunk_store_p(uint16_t* t, const u32x4 (&v)[2]) {
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int e = threadIdx.x + 256 * u;
+    *reinterpret_cast<u32x4*>(t + poff(kperm(e >> 3), e & 7)) = v[u];
+  }
+}
+
+// Chunk staging of the key-split kernels.  Thread t moves 16-byte piece
 // t % 8 of rows t / 8 + 32 u (u = 0..3) of a 128-row chunk.  Rows 0..63 of
 // a chunk always lie in the image (every chunk holds 128 rows but a tail,
 // which holds 64); rows 64..127 of a tail are fetched from the image's last
@@ -613,7 +656,7 @@ __device__ __forceinline__ void stage2(u32x4 (&a)[4], u32x4 (&b)[4], const uint1
 }
 
 // staged rows into two tiles at this thread's offsets oa, ob (row t / 8;
-// rows + 32 u sit 32 * 64 elements further: kperm and swz leave the bits
+// rows + 32 u sit 32 * 64 elements further: the permutations leave the bits
 // from 5 up alone); `full`: the chunk holds 128 rows
 __device__ __forceinline__ void put2(uint16_t* ta, int oa, uint16_t* tb, int ob,
                                      const u32x4 (&a)[4], const u32x4 (&b)[4], bool full) {
@@ -624,6 +667,278 @@ __device__ __forceinline__ void put2(uint16_t* ta, int oa, uint16_t* tb, int ob,
     *reinterpret_cast<u32x4*>(tb + ob + 32 * HD * u) = b[u];
   }
 }
+
+// W partial [64][OPAD] tiles in LDS -> their sum times f as bf16 in 64 rows
+// of 64 channels: thread t writes 16 channels of row t / 4
+template <int W>
+__device__ __forceinline__ void merge_rows(const float* part, float f, uint16_t* dst,
+                                           long stride) {
+  const int q = threadIdx.x >> 2, d0 = (threadIdx.x & 3) * 16;
+  uint32_t pk[8];
+#pragma unroll
+  for (int j = 0; j < 16; j += 2) {
+    float v[2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const int ix = q * OPAD + d0 + j + e;
+      v[e] = part[ix];
+#pragma unroll
+      for (int k = 1; k < W; ++k) v[e] += part[k * QT * OPAD + ix];
+    }
+    pk[j / 2] = (uint32_t)bf(v[0] * f) | ((uint32_t)bf(v[1] * f) << 16);
+  }
+  uint4* p = reinterpret_cast<uint4*>(dst + (long)q * stride + d0);
+  p[0] = uint4{pk[0], pk[1], pk[2], pk[3]};
+  p[1] = uint4{pk[4], pk[5], pk[6], pk[7]};
+}
+
+__global__ __launch_bounds__(256, 2) void k_attn_bwd_q_r(const uint16_t* qkv, const uint16_t* o,
+                                                         const uint16_t* dout, const float* lse,
+                                                         int L, int C, uint16_t* dqkv,
+                                                         float* dsum) {
+  // two stages of K and V chunks during the key loop, then the four waves'
+  // dq^T partials
+  __shared__ __attribute__((aligned(16))) float smem[4 * QT * OPAD];
+  __shared__ float Ds[QT];
+  static_assert(4 * KS_CHUNK * HD * sizeof(uint16_t) <= sizeof(smem), "two stages fit");
+  uint16_t* buf = reinterpret_cast<uint16_t*>(smem);
+  int qt, h, b;
+  tile_of(qt, h, b);
+  const int H = gridDim.y;
+  const long row0 = (long)b * L;
+  const long C3 = 3L * C;
+  const uint16_t* base = qkv + row0 * C3 + h * HD;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int m = lane & 15, g = lane >> 4;
+  const int q0 = qt * QT;
+  const long lrow = ((long)b * H + h) * L + q0;  // lse / D index of the tile's first row
+  const uint16_t* dbase = dout + (row0 + q0) * C + h * HD;
+  // every load of the prologue is issued before the first wait
+  const long po = piece(C3);
+  u32x4 rk[4], rv[4];
+  stage2(rk, rv, base + C, base + 2 * C, C3, po, 0, L);
+  bf16x8 od[2], oo[2];  // dO and o of query 16 w + m, whose D this wave sums
+#pragma unroll
+  for (int kk = 0; kk < 2; ++kk) {
+    const long r = (long)(16 * w + m) * C + 32 * kk + 8 * g;
+    od[kk] = *reinterpret_cast<const bf16x8*>(dbase + r);
+    oo[kk] = *reinterpret_cast<const bf16x8*>(o + (row0 + q0) * C + h * HD + r);
+  }
+  bf16x8 qa[4][2], da[4][2];
+#pragma unroll
+  for (int qb = 0; qb < 4; ++qb)
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) {
+      const int r = 16 * qb + m, e = 32 * kk + 8 * g;
+      qa[qb][kk] = *reinterpret_cast<const bf16x8*>(base + (long)(q0 + r) * C3 + e);
+      da[qb][kk] = *reinterpret_cast<const bf16x8*>(dbase + (long)r * C + e);
+    }
+  float nD[4], nl[4];  // -D and -lse (log2 domain) of query 16 qb + m
+#pragma unroll
+  for (int qb = 0; qb < 4; ++qb) nl[qb] = -lse[lrow + 16 * qb + m] * LOG2E;
+  const int ko = poff(kperm(threadIdx.x >> 3), threadIdx.x & 7);
+  {
+    // the lanes m, m + 16, m + 32, m + 48 hold the query's 64 channels
+    float d = dot8(od[0], oo[0]) + dot8(od[1], oo[1]);
+    d += __shfl_xor(d, 16, 64);
+    d += __shfl_xor(d, 32, 64);
+    if (g == 0) {
+      dsum[lrow + 16 * w + m] = d;
+      Ds[16 * w + m] = d;
+    }
+  }
+  __syncthreads();  // Ds
+  f32x4 acc[4][HD / 16];
+#pragma unroll
+  for (int qb = 0; qb < 4; ++qb) {
+    nD[qb] = -Ds[16 * qb + m];
+#pragma unroll
+    for (int db = 0; db < HD / 16; ++db) acc[qb][db] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  const int nch = (L + KS_CHUNK - 1) / KS_CHUNK;
+  for (int kc = 0; kc < nch; ++kc) {
+    const int rows = min(KS_CHUNK, L - kc * KS_CHUNK);
+    uint16_t* Ks = buf + (kc & 1) * 2 * KS_CHUNK * HD;
+    uint16_t* Vs = Ks + KS_CHUNK * HD;
+    // this stage was last read two chunks ago, before the previous barrier
+    put2(Ks, ko, Vs, ko, rk, rv, rows == KS_CHUNK);
+    __syncthreads();
+    stage2(rk, rv, base + C, base + 2 * C, C3, po, min(kc + 1, nch - 1) * KS_CHUNK, L);
+    if (32 * w >= rows) continue;  // no keys of this wave in a 64-key tail chunk
+
+    bf16x8 ds[4];
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb) {
+      const int r = 32 * w + 16 * kb + m;
+      const bf16x8 k0 = frag_row_p(Ks, r, 0, g), k1 = frag_row_p(Ks, r, 1, g);
+      const bf16x8 v0 = frag_row_p(Vs, r, 0, g), v1 = frag_row_p(Vs, r, 1, g);
+#pragma unroll
+      for (int qb = 0; qb < 4; ++qb) {
+        const f32x4 s = mma(k1, qa[qb][1], mma(k0, qa[qb][0], f32x4{0.f, 0.f, 0.f, 0.f}));
+        const f32x4 dp = mma(
+            v1, da[qb][1], mma(v0, da[qb][0], f32x4{nD[qb], nD[qb], nD[qb], nD[qb]}));
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          ds[qb][4 * kb + i] = (__bf16)(ex2(fmaf(s[i], SCALE * LOG2E, nl[qb])) * dp[i]);
+      }
+    }
+#pragma unroll
+    for (int db = 0; db < HD / 16; ++db) {
+      const bf16x8 ka = frag_tr_p(Ks, 32 * w, 16 * db, lane);
+#pragma unroll
+      for (int qb = 0; qb < 4; ++qb) acc[qb][db] = mma(ka, ds[qb], acc[qb][db]);
+    }
+  }
+  __syncthreads();  // every wave is done with the K and V chunks
+  float* part = smem + w * QT * OPAD;
+#pragma unroll
+  for (int qb = 0; qb < 4; ++qb)
+#pragma unroll
+    for (int db = 0; db < HD / 16; ++db)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        part[(16 * qb + m) * OPAD + 16 * db + 4 * g + i] = acc[qb][db][i];
+  __syncthreads();
+  merge_rows<4>(smem, SCALE, dqkv + (row0 + q0) * C3 + h * HD, C3);
+}
+
+__global__ __launch_bounds__(256, 2) void k_attn_bwd_kv_r(const uint16_t* qkv,
+                                                          const uint16_t* dout, const float* lse,
+                                                          const float* dsum, int L, int C,
+                                                          uint16_t* dqkv) {
+  // two stages of Q and dO chunks during the query loop (stage s at
+  // s * 2 * KC * HD), then the query halves' dv^T and dk^T partials
+  __shared__ __attribute__((aligned(16))) float smem[4 * QT * OPAD];
+  static_assert(4 * KC * HD * sizeof(uint16_t) <= sizeof(smem), "two stages fit");
+  uint16_t* buf = reinterpret_cast<uint16_t*>(smem);
+  int kt, h, b;
+  tile_of(kt, h, b);
+  const int H = gridDim.y;
+  const long row0 = (long)b * L;
+  const long C3 = 3L * C;
+  const uint16_t* base = qkv + row0 * C3 + h * HD;
+  const uint16_t* dbase = dout + row0 * C + h * HD;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int m = lane & 15, g = lane >> 4;
+  const int wk = w & 1, wq = w >> 1;
+  const int k0 = kt * QT;
+  // lse and D of the queries this lane holds: 32 wq + 8 g + 4 qb + i of a chunk
+  const float* lrow = lse + ((long)b * H + h) * L + 32 * wq + 8 * g;
+  const float* drow = dsum + ((long)b * H + h) * L + 32 * wq + 8 * g;
+  bf16x8 ka[2][2], va[2][2];
+#pragma unroll
+  for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) {
+      const uint16_t* p = base + (long)(k0 + 32 * wk + 16 * kb + m) * C3 + 32 * kk + 8 * g;
+      ka[kb][kk] = *reinterpret_cast<const bf16x8*>(p + C);
+      va[kb][kk] = *reinterpret_cast<const bf16x8*>(p + 2 * C);
+    }
+  f32x4 dv[2][HD / 16], dk[2][HD / 16];
+#pragma unroll
+  for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+    for (int db = 0; db < HD / 16; ++db) {
+      dv[kb][db] = f32x4{0.f, 0.f, 0.f, 0.f};
+      dk[kb][db] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+  const int nch = L / KC;
+  u32x4 rq[2], rd[2];
+  f32x4 nl[2], nD[2];  // of the next chunk until the top of its iteration
+  chunk_regs(rq, base, C3);
+  chunk_regs(rd, dbase, C);
+#pragma unroll
+  for (int qb = 0; qb < 2; ++qb) {
+    nl[qb] = *reinterpret_cast<const f32x4*>(lrow + 4 * qb);
+    nD[qb] = *reinterpret_cast<const f32x4*>(drow + 4 * qb);
+  }
+  for (int qc = 0; qc < nch; ++qc) {
+    uint16_t* Qs = buf + (qc & 1) * 2 * KC * HD;
+    uint16_t* dOs = Qs + KC * HD;
+    // this stage was last read two chunks ago, before the previous barrier
+    chunk_store_p(Qs, rq);
+    chunk_store_p(dOs, rd);
+    f32x4 l[2], D[2];
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb) {
+      l[qb] = nl[qb] * -LOG2E;
+      D[qb] = -nD[qb];
+    }
+    __syncthreads();
+    {
+      const int qn = min(qc + 1, nch - 1);  // unconditional: the wait stays at the store
+      chunk_regs(rq, base + (long)qn * KC * C3, C3);
+      chunk_regs(rd, dbase + (long)qn * KC * C, C);
+#pragma unroll
+      for (int qb = 0; qb < 2; ++qb) {
+        nl[qb] = *reinterpret_cast<const f32x4*>(lrow + qn * KC + 4 * qb);
+        nD[qb] = *reinterpret_cast<const f32x4*>(drow + qn * KC + 4 * qb);
+      }
+    }
+    bf16x8 p[2], ds[2];
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb) {
+      const int r = 32 * wq + 16 * qb + m;
+      const bf16x8 q0 = frag_row_p(Qs, r, 0, g), q1 = frag_row_p(Qs, r, 1, g);
+      const bf16x8 d0 = frag_row_p(dOs, r, 0, g), d1 = frag_row_p(dOs, r, 1, g);
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb) {
+        const f32x4 s = mma(q1, ka[kb][1], mma(q0, ka[kb][0], f32x4{0.f, 0.f, 0.f, 0.f}));
+        const f32x4 dp = mma(d1, va[kb][1], mma(d0, va[kb][0], D[qb]));
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float e = ex2(fmaf(s[i], SCALE * LOG2E, l[qb][i]));
+          p[kb][4 * qb + i] = (__bf16)e;
+          ds[kb][4 * qb + i] = (__bf16)(e * dp[i]);
+        }
+      }
+    }
+#pragma unroll
+    for (int db = 0; db < HD / 16; ++db) {
+      const bf16x8 dt = frag_tr_p(dOs, 32 * wq, 16 * db, lane);
+      const bf16x8 qt = frag_tr_p(Qs, 32 * wq, 16 * db, lane);
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb) {
+        dv[kb][db] = mma(dt, p[kb], dv[kb][db]);
+        dk[kb][db] = mma(qt, ds[kb], dk[kb][db]);
+      }
+    }
+  }
+  __syncthreads();  // every wave is done with the chunks
+  float* part = smem + wq * QT * OPAD;
+#pragma unroll
+  for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+    for (int db = 0; db < HD / 16; ++db)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int ix = (32 * wk + 16 * kb + m) * OPAD + 16 * db + 4 * g + i;
+        part[ix] = dk[kb][db][i];
+        part[2 * QT * OPAD + ix] = dv[kb][db][i];
+      }
+  __syncthreads();
+  uint16_t* out = dqkv + (row0 + k0) * C3 + h * HD;
+  merge_rows<2>(smem, SCALE, out + C, C3);
+  merge_rows<2>(smem + 2 * QT * OPAD, 1.f, out + 2 * C, C3);
+}
+
+// ---------------------------------------------------------------------------
+// forward, key-split form (any L): block (64-query tile, head, image).  The
+// keys stream through LDS 128 at a time and wave w takes keys 32 w .. + 31
+// of every chunk for all 64 queries, so each K or V fragment read from LDS
+// feeds four MFMAs (one per 16-query block) and p never leaves registers:
+//   s^T = k q^T   A = k rows (LDS), B = q (registers); the output lane
+//                 (g, m) holds keys 8 g + 4 kb + i of query 16 qb + m
+//   o^T += v^T p^T  A = v read down the tile (lane (g, j): keys 8 g + t of
+//                 channel 16 db + j), B = p^T (lane (g, m): keys 8 g + t of
+//                 query m, t = 4 kb + i: exactly the values the lane holds)
+// For the first product to deliver keys 8 g + 4 kb + i on output row 4 g + i
+// of block kb, every 32-key group is stored with its rows permuted: key k at
+// row (k & 3) | ((k >> 3) & 3) << 2 | ((k >> 2) & 1) << 4, so that rows
+// 16 kb .. 16 kb + 15 hold keys 8 (m >> 2) + 4 kb + (m & 3), m = 0..15.
+// Every wave keeps a running maximum and sum per query (online softmax); at
+// the end the four partial states are merged through LDS.
+// ---------------------------------------------------------------------------
 
 // Softmax of the key-split forward: each wave keeps, per query, a reference
 // r in the log2 domain (scores times SCALE * LOG2E).  Its weights are
@@ -769,29 +1084,27 @@ __global__ __launch_bounds__(256, 2) void k_attn_fwd_ks(const uint16_t* qkv, int
       lse[((long)b * H + h) * L + q0 + q] = (R + log2f(l)) * LN2;
   }
   __syncthreads();
-  // 64 queries x 64 channels: thread t writes 16 channels of query t / 4
-  {
-    const int q = threadIdx.x >> 2, d0 = (threadIdx.x & 3) * 16;
-    uint32_t pk[8];
-#pragma unroll
-    for (int j = 0; j < 16; j += 2) {
-      const int ix = q * OPAD + d0 + j;
-      const float v0 = smem[ix] + smem[QT * OPAD + ix] + smem[2 * QT * OPAD + ix] +
-                       smem[3 * QT * OPAD + ix];
-      const float v1 = smem[ix + 1] + smem[QT * OPAD + ix + 1] + smem[2 * QT * OPAD + ix + 1] +
-                       smem[3 * QT * OPAD + ix + 1];
-      pk[j / 2] = (uint32_t)bf(v0) | ((uint32_t)bf(v1) << 16);
-    }
-    uint4* dst = reinterpret_cast<uint4*>(o + (row0 + q0 + q) * C + h * HD + d0);
-    dst[0] = uint4{pk[0], pk[1], pk[2], pk[3]};
-    dst[1] = uint4{pk[4], pk[5], pk[6], pk[7]};
-  }
+  merge_rows<4>(smem, 1.f, o + (row0 + q0) * C + h * HD, C);
 }
 
 }  // namespace
 
 bool attn_fits(int L, int C, int heads) {
   return L >= QT && L % QT == 0 && L <= ATTN_LMAX && C == heads * HD;
+}
+
+// Which streamed backward.  The kernels with p and ds in registers fill a CU,
+// so that no weight-gradient block of the other stream runs beside them; they
+// pay once a block's loop over the other side is long or the grid fills the
+// GPU (two blocks per CU).  A training iteration of 1 + 1 blocks, us, LDS
+// strips against registers: 1 x 2048 tokens of 4 heads 528 against 467, of 8
+// 657 against 611, 2 x 1536 of 12 1131 against 1067, 4 x 1024 of 12 1164
+// against 1142, 8 x 512 of 12 (768 blocks) the same, 16 x 512 1783 against
+// 1768; below the line 1 x 1024 of 8 467 against 473, 4 x 512 of 12 754
+// against 767, and for the whole-head kernels 16 x 128 of 12 741 against 758,
+// 16 x 256 990 against 987.
+static bool attn_bwd_long(int B, int L, int heads) {
+  return L > 256 && (L >= 2048 || (long)B * heads * (L / QT) >= 512);
 }
 
 template <int L>
@@ -826,19 +1139,20 @@ hipError_t launch_attn_bwd(const void* qkv, const void* o, const void* dout, con
     case 128: return attn_bwd_t<128>(qkv, o, dout, lse, B, C, heads, dqkv, dsum, st);
     case 192: return attn_bwd_t<192>(qkv, o, dout, lse, B, C, heads, dqkv, dsum, st);
     case 256: return attn_bwd_t<256>(qkv, o, dout, lse, B, C, heads, dqkv, dsum, st);
-    default: {
-      hipLaunchKernelGGL(k_attn_bwd_q_s, dim3(L / QT, heads, B), dim3(256), 0, st,
-                         static_cast<const uint16_t*>(qkv), static_cast<const uint16_t*>(o),
-                         static_cast<const uint16_t*>(dout), lse, L, C,
-                         static_cast<uint16_t*>(dqkv), dsum);
-      hipError_t e = hipGetLastError();
-      if (e != hipSuccess) return e;
-      hipLaunchKernelGGL(k_attn_bwd_kv_s, dim3(L / QT, heads, B), dim3(256), 0, st,
-                         static_cast<const uint16_t*>(qkv), static_cast<const uint16_t*>(dout),
-                         lse, dsum, L, C, static_cast<uint16_t*>(dqkv));
-      return hipGetLastError();
-    }
+    default: break;
   }
+  const bool wide = attn_bwd_long(B, L, heads);
+  const dim3 grid(L / QT, heads, B);
+  hipLaunchKernelGGL(wide ? k_attn_bwd_q_r : k_attn_bwd_q_s, grid, dim3(256), 0, st,
+                     static_cast<const uint16_t*>(qkv), static_cast<const uint16_t*>(o),
+                     static_cast<const uint16_t*>(dout), lse, L, C,
+                     static_cast<uint16_t*>(dqkv), dsum);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(wide ? k_attn_bwd_kv_r : k_attn_bwd_kv_s, grid, dim3(256), 0, st,
+                     static_cast<const uint16_t*>(qkv), static_cast<const uint16_t*>(dout), lse,
+                     dsum, L, C, static_cast<uint16_t*>(dqkv));
+  return hipGetLastError();
 }
 
 }  // namespace pulse

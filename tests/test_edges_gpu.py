@@ -6,9 +6,11 @@ import numpy as np
 import pytest
 
 from oracle import pulse_oracle as O
+from oracle import transformer_oracle as TO
 from paper_2606_19163_amd import configs, synth
+from paper_2606_19163_amd import tstage as TS
 
-from gpu_util import compare, log, run_gpu
+from gpu_util import compare, log, rel_l2, run_gpu
 
 pytestmark = pytest.mark.gpu
 
@@ -86,3 +88,33 @@ BIAS = [(configs.BF16, 1, 8, 8, 320), (configs.BF16, 2, 33, 20, 448), (configs.B
 @pytest.mark.parametrize("dtype,batch,h,w,c", BIAS, ids=[f"{d}-{b}x{h}x{w}x{c}" for d, b, h, w, c in BIAS])
 def test_bias_gradients(dtype, batch, h, w, c):
     _parity(_pair(batch, h, w, c, 32, 64, dtype, 1), 25, f"bias {dtype} {batch}x{h}x{w}x{c}")
+
+
+# Attention backward with p and ds in registers: from 2048 tokens on, and from
+# 512 blocks on beyond 256 tokens; both lengths end in half a 128-key chunk.
+@pytest.mark.parametrize("batch,tokens,heads", [(1, 2112, 2), (14, 320, 8)])
+def test_attention_backward_in_registers(batch, tokens, heads):
+    import torch
+    d = configs._tstage(batch, tokens, 64 * heads, heads, 1, 1)
+    d["mlp"] = 2
+    p, b = synth.make_tstage(d, 26)
+    log(f"case attention backward: B={batch} tokens={tokens} heads={heads}")
+    ref = TO.tstage_run(d, p, b["x"], b["u"], b["g_enc"], b["g_dec"])
+    st = TS.TStage(d)
+    st.set_params(p)
+    dev = {k: st.to_dev(v) for k, v in b.items()}
+    runs = []
+    for _ in range(2):
+        st.zero_grads()
+        st.forward(TS.ENC, 0, dev["x"])
+        st.forward(TS.DEC, 0, dev["u"])
+        du = st.backward(TS.DEC, 0, dev["g_dec"]).clone()
+        dx = st.backward(TS.ENC, 0, dev["g_enc"]).clone()
+        torch.cuda.synchronize()
+        runs.append(dict(st.grads_dict(), du=du.float().cpu().numpy(),
+                         dx=dx.float().cpu().numpy()))
+    want = dict(ref["grads"], du=ref["du"], dx=ref["dx"])
+    for k, v in want.items():
+        assert np.array_equal(runs[0][k], runs[1][k]), k  # reruns are bitwise identical
+        e = rel_l2(runs[0][k], v)
+        assert e < 2e-2, (k, e)  # bf16 activations and weights, fp32 sums
