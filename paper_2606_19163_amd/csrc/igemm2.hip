@@ -892,6 +892,10 @@ __device__ __forceinline__ void rd_f32x16(float (&v)[16], uint32_t a0, uint32_t 
 // hold as they are, so there is nothing to transpose.  Bound by the fp32 MFMA
 // rate (32 cycles each): a wave of 32 x 32 issues 16 MFMAs per 16 reads, and
 // the other waves of the SIMD cover the reads' wait.
+// An fp32 sum of n products in a row is off by about sqrt(n) roundings, and a
+// pixel split holds thousands of pixels: every WF_FOLD K-steps (256 pixels)
+// the MFMAs' sums move to a second accumulator (16 adds per 256 MFMAs).
+constexpr int WF_FOLD = 4;
 template <class C, bool BIAS, class Issue>
 __device__ __forceinline__ void wgrad_loop_f32(uint32_t sbase, char* smem, int KT, int wm, int wn,
                                                int lane, Issue& issue,
@@ -908,10 +912,24 @@ __device__ __forceinline__ void wgrad_loop_f32(uint32_t sbase, char* smem, int K
     rb[i] = (uint32_t)(g4 * C::PB + rot_slot(cb >> 2, g4, C::CB, C::RB_A, C::RB_B) * 16 +
                        (cb & 3) * 4);
   }
+  f32x4_t sum[C::TM][C::TN];
+#pragma unroll
+  for (int i = 0; i < C::TM; ++i)
+#pragma unroll
+    for (int j = 0; j < C::TN; ++j) sum[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  auto fold = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < C::TM; ++i)
+#pragma unroll
+      for (int j = 0; j < C::TN; ++j) {
+        sum[i][j] += acc[i][j];
+        acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+      }
+  };
   float v[2][16];
   // quarter q's 16 MFMAs once its values have landed, with quarter q + 1's
   // reads (all 16 pixels further on) issued before them
-  auto quarter = [&](uint32_t sb, bool sum, auto q_tag) __attribute__((always_inline)) {
+  auto quarter = [&](uint32_t sb, bool bias, auto q_tag) __attribute__((always_inline)) {
     constexpr int Q = decltype(q_tag)::value;
     float(&x)[16] = v[Q & 1];
     lgkm_wait<0>();
@@ -928,7 +946,7 @@ __device__ __forceinline__ void wgrad_loop_f32(uint32_t sbase, char* smem, int K
         for (int j = 0; j < 2; ++j)
           acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[4 * s + i], x[4 * s + 2 + j],
                                                            acc[i][j], 0, 0, 0);
-    if (sum && wn == (Q >> 1)) {
+    if (bias && wn == (Q >> 1)) {
       ds_add<0>(bslot, (x[0] + x[4]) + (x[8] + x[12]));
       ds_add<64>(bslot, (x[1] + x[5]) + (x[9] + x[13]));
     }
@@ -941,13 +959,18 @@ __device__ __forceinline__ void wgrad_loop_f32(uint32_t sbase, char* smem, int K
     const uint32_t sb = sbase + (uint32_t)((kt & 1) * C::STAGE);
     rd_f32x16<C, 0>(v[0], sb + ra[0], sb + ra[1], sb + rb[0], sb + rb[1]);
     if (kt + 1 < KT) issue(kt + 1, smem + ((kt + 1) & 1) * C::STAGE);
-    const bool sum = BIAS && kt == kb;
-    if (sum) kb += kbstep;
-    quarter(sb, sum, std::integral_constant<int, 0>());
-    quarter(sb, sum, std::integral_constant<int, 1>());
-    quarter(sb, sum, std::integral_constant<int, 2>());
-    quarter(sb, sum, std::integral_constant<int, 3>());
+    const bool bias = BIAS && kt == kb;
+    if (bias) kb += kbstep;
+    quarter(sb, bias, std::integral_constant<int, 0>());
+    quarter(sb, bias, std::integral_constant<int, 1>());
+    quarter(sb, bias, std::integral_constant<int, 2>());
+    quarter(sb, bias, std::integral_constant<int, 3>());
+    if (kt % WF_FOLD == WF_FOLD - 1) fold();
   }
+#pragma unroll
+  for (int i = 0; i < C::TM; ++i)
+#pragma unroll
+    for (int j = 0; j < C::TN; ++j) acc[i][j] += sum[i][j];
 }
 
 }  // namespace

@@ -372,7 +372,8 @@ int pick_splits(const pulse_stage* s, int tile, int M, int N, int& kchunk) {
   const long tiles = (long)((M + ti.bm - 1) / ti.bm) * ((N + ti.bn - 1) / ti.bn);
   // resident blocks (fp32: one fills a CU's matrix cores)
   const long slots = 256L * (s->dtype == DT_F32 ? 1 : std::min(ti.per_cu, 2));
-  // s per CU (fp32: the nominal matrix rate is a sixteenth)
+  // s per CU at the loops' rates (fp32: a tenth of bf16's; large products on
+  // this card reach 153 against 1294 TFLOP/s)
   const double t_tile = 2.0 * ti.bm * ti.bn * (double)s->P / (s->dtype == DT_F32 ? 3.0e11 : 3.0e12);
   const double t_elem = (double)M * N / 4.0e12;                       // s per byte per element
   const long maxs = std::max(1L, (long)(s->P / (4 * ti.bk)));          // >= 4 K-steps each

@@ -90,6 +90,25 @@ def test_bias_gradients(dtype, batch, h, w, c):
     _parity(_pair(batch, h, w, c, 32, 64, dtype, 1), 25, f"bias {dtype} {batch}x{h}x{w}x{c}")
 
 
+def test_fp32_weight_gradient_sums():
+    """Long pixel sums of an fp32 weight gradient (24576 pixels of 192
+    channels): the shortcut's, over the decoder input and the output gradient,
+    which are exact inputs.  Values added one by one in fp32 are off by 0.45 u
+    sqrt(n / 2) of their sum, u = 2^-24 (0.45 u: a rounding's root mean
+    square): 3.0e-7 for the 256 pixels of one accumulator and 1.9e-7 for 96
+    such sums, 3.5e-7 together; twice that is allowed.  One accumulator over a
+    pixel split of 4096 to 8192 is off by 1.2e-6 to 1.7e-6."""
+    desc = _pair(8, 48, 64, 192, 32, 64, configs.F32, 1)
+    log("case fp32 sums: B=8 48x64x192 seed=27")
+    params, b = synth.make_all(desc, 27)
+    gpu, _ = run_gpu(desc, params, b, want_cache=False)
+    u = np.asarray(b["u"], np.float64).reshape(-1, 192)
+    g = np.asarray(b["g_dec"], np.float64).reshape(-1, 192)
+    e = rel_l2(gpu["grads"]["dec0.Ws"][:, :192], g.T @ u)
+    log(f"  fp32 sums dec0.Ws = {e:.3e}")
+    assert e < 7e-7, e
+
+
 # Attention backward with p and ds in registers: from 2048 tokens on, and from
 # 512 blocks on beyond 256 tokens; both lengths end in half a 128-key chunk.
 @pytest.mark.parametrize("batch,tokens,heads", [(1, 2112, 2), (14, 320, 8)])
