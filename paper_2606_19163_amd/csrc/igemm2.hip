@@ -26,6 +26,7 @@
 
 #include "common.hpp"
 #include "kernels.hpp"
+#include "kpos.hpp"
 
 namespace pulse {
 
@@ -476,15 +477,13 @@ __global__ __launch_bounds__(C::NT) void igemm2_conv(GemmArgs a) {
   // divisions.  The weight column of (tap, channel c) is begin + tap*C + c.
   SegRt cur = seg_rt<C::ESZ>(a.seg[0], P);
   int iseg = 0, itap = 0, icb = 0, idy, idx;
-  if (kt0 > 0) {
-    int q = kt0;  // first K-step of this split
-    while (iseg < 2 && q >= cur.taps * (cur.C / C::BK)) {
-      q -= cur.taps * (cur.C / C::BK);
-      ++iseg;
-      select_into(cur, iseg == 1, q1, q2);
-    }
-    icb = (q / cur.taps) * C::BK;
-    itap = q - (q / cur.taps) * cur.taps;
+  if (kt0 > 0) {  // a later split or K group
+    const KStart k = k_start(kt0, C::BK, KSeg{cur.taps, cur.C}, KSeg{q1.taps, q1.C},
+                             KSeg{q2.taps, q2.C});
+    if (k.seg > 0) select_into(cur, k.seg == 1, q1, q2);
+    iseg = k.seg;
+    itap = k.tap;
+    icb = k.cb;
     idy = cur.taps == 9 ? itap / 3 - 1 : 0;
     idx = cur.taps == 9 ? itap % 3 - 1 : 0;
   } else {
