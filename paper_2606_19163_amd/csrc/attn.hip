@@ -1093,10 +1093,10 @@ bool attn_fits(int L, int C, int heads) {
   return L >= QT && L % QT == 0 && L <= ATTN_LMAX && C == heads * HD;
 }
 
-// Which streamed backward.  The kernels with p and ds in registers fill a CU,
-// so that no weight-gradient block of the other stream runs beside them; they
-// pay once a block's loop over the other side is long or the grid fills the
-// GPU (two blocks per CU).  A training iteration of 1 + 1 blocks, us, LDS
+// Which streamed backward (more than 256 tokens).  The kernels with p and ds
+// in registers fill a CU, so that no weight-gradient block of the other stream
+// runs beside them; they pay once a block's loop over the other side is long
+// or the grid fills the GPU (two blocks per CU).  A training iteration of 1 + 1 blocks, us, LDS
 // strips against registers: 1 x 2048 tokens of 4 heads 528 against 467, of 8
 // 657 against 611, 2 x 1536 of 12 1131 against 1067, 4 x 1024 of 12 1164
 // against 1142, 8 x 512 of 12 (768 blocks) the same, 16 x 512 1783 against
@@ -1104,7 +1104,7 @@ bool attn_fits(int L, int C, int heads) {
 // against 767, and for the whole-head kernels 16 x 128 of 12 741 against 758,
 // 16 x 256 990 against 987.
 static bool attn_bwd_long(int B, int L, int heads) {
-  return L > 256 && (L >= 2048 || (long)B * heads * (L / QT) >= 512);
+  return L >= 2048 || (long)B * heads * (L / QT) >= 512;
 }
 
 template <int L>

@@ -1423,7 +1423,6 @@ using C2_64x64G2 = CfgC<64, 64, 32, 32, 3, 64, false, 2>;
 using C2_128x160K32 = CfgC<128, 160, 64, 80, 4, 32>;
 using C2_128x128K32 = CfgC<128, 128, 64, 64, 4, 32>;
 using C2_64x96K32 = CfgC<64, 96, 32, 48, 4, 32>;
-using C2_64x64K32 = CfgC<64, 64, 32, 32, 4, 32>;
 // fp32
 using C2_F64x64 = CfgC<64, 64, 32, 32, 3, 32, true>;
 using C2_F64x32 = CfgC<64, 32, 32, 16, 3, 32, true>;
@@ -1537,7 +1536,6 @@ static auto with_conv(int t, F f) {
     case TILE2_C128x160K32: return f(C2_128x160K32());
     case TILE2_C128x128K32: return f(C2_128x128K32());
     case TILE2_C64x96K32: return f(C2_64x96K32());
-    case TILE2_C64x64K32: return f(C2_64x64K32());
     case TILE2_F64x64: return f(C2_F64x64());
     case TILE2_F64x32: return f(C2_F64x32());
     case TILE2_F32x32: return f(C2_F32x32());

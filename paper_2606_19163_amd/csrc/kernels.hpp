@@ -110,10 +110,9 @@ enum Tile2 : int {
   TILE2_C128x160K32 = 8,
   TILE2_C128x128K32 = 9,
   TILE2_C64x96K32 = 10,
-  TILE2_C64x64K32 = 11,
-  TILE2_F64x64 = 12,    // fp32, 4 waves of 32 x 32
-  TILE2_F64x32 = 13,    // fp32, 4 waves of 32 x 16
-  TILE2_F32x32 = 14,    // fp32, 4 waves of 16 x 16
+  TILE2_F64x64 = 11,    // fp32, 4 waves of 32 x 32
+  TILE2_F64x32 = 12,    // fp32, 4 waves of 32 x 16
+  TILE2_F32x32 = 13,    // fp32, 4 waves of 16 x 16
   TILE2_W320x128 = 20,  // 8 waves of 80 x 64, one block per CU
   TILE2_W128x128 = 21,  // 4 waves of 64 x 64
   TILE2_WGRAD_FIRST = 20,

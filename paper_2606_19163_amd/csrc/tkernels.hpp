@@ -33,12 +33,10 @@ hipError_t launch_attn_bwd(const void* qkv, const void* o, const void* dout, con
 hipError_t launch_ln_fwd(const void* x, long T, int C, float eps, const float* g, const float* b,
                          void* y, float* stats, hipStream_t st);
 // dx = add + d LN / dx (add [T][C] bf16 or null); part[ln_bwd_blocks(T, C)][3][C]
-// receives per-block column sums of dy * xhat, dy and dx as stored.  done
-// (may be null): an event recorded by the kernel's own completion.
+// receives per-block column sums of dy * xhat, dy and dx as stored.
 int ln_bwd_blocks(long T, int C);
 hipError_t launch_ln_bwd(const void* dy, const void* x, const float* stats, const float* g,
-                         const void* add, long T, int C, void* dx, float* part, hipStream_t st,
-                         hipEvent_t done = nullptr);
+                         const void* add, long T, int C, void* dx, float* part, hipStream_t st);
 // dg += row 0, db += row 1, dsum (or null) += row 2 of part[rows][3][C]
 hipError_t launch_ln_totals(const float* part, int rows, int C, float* dg, float* db, float* dsum,
                             hipStream_t st);

@@ -1,7 +1,6 @@
 // LayerNorm and GELU of the transformer-block stage (gfx950): token-major
 // [T][C] bf16 activations; one wave per token for the LayerNorm, each lane
 // holding whole 8-channel vectors in registers; statistics in fp32.
-#include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -290,8 +289,7 @@ hipError_t launch_ln_fwd(const void* x, long T, int C, float eps, const float* g
 }
 
 hipError_t launch_ln_bwd(const void* dy, const void* x, const float* stats, const float* g,
-                         const void* add, long T, int C, void* dx, float* part, hipStream_t st,
-                         hipEvent_t done) {
+                         const void* add, long T, int C, void* dx, float* part, hipStream_t st) {
   if (C % 8 || C > 64 * 8 * LN_VEC) return hipErrorInvalidValue;
   auto kern = C <= 512 ? k_ln_bwd<1, 4> : C <= 1024 ? k_ln_bwd<2, 2> : C <= 1536 ? k_ln_bwd<3, 1>
                                                                                   : k_ln_bwd<4, 1>;
@@ -301,11 +299,7 @@ hipError_t launch_ln_bwd(const void* dy, const void* x, const float* stats, cons
   const float2* ss = reinterpret_cast<const float2*>(stats);
   const uint16_t* ad = static_cast<const uint16_t*>(add);
   uint16_t* o = static_cast<uint16_t*>(dx);
-  if (done)  // the event completes with the kernel (no marker packet of its own)
-    hipExtLaunchKernelGGL(kern, grid, block, 0, st, nullptr, done, 0, d, xi, ss, g, ad, (int)T, C, o,
-                          part);
-  else
-    hipLaunchKernelGGL(kern, grid, block, 0, st, d, xi, ss, g, ad, (int)T, C, o, part);
+  hipLaunchKernelGGL(kern, grid, block, 0, st, d, xi, ss, g, ad, (int)T, C, o, part);
   return hipGetLastError();
 }
 
