@@ -271,6 +271,7 @@ long conv_tiles(const pulse_stage* s, int tile, int N) { return conv_tile_count(
 // Tile shape of a conv-mode GEMM with N output columns, before the small-grid
 // plan of the 64-channel stages.
 int conv_tile(const pulse_stage* s, int N) {
+  if (s->conv_tile_force >= 0) return s->conv_tile_force;
   if (s->dtype == DT_F32) {
     // fp32 MFMAs bound these: the tile whose rounds of one block per CU cost
     // least, a K-step of bm x bn taking about 0.19 us + 0.15 us per 1024
@@ -300,7 +301,6 @@ int conv_tile(const pulse_stage* s, int N) {
     const bool wasteful = 5L * ((N + bn - 1) / bn) * bn > 6L * ((N + 95) / 96) * 96;
     return conv_tiles(s, big, N) >= 200 && !wasteful ? big : TILE2_C64x96K32;
   }
-  if (s->conv_tile_force >= 0) return s->conv_tile_force;
   return N % 160 == 0 ? TILE2_C128x160 : TILE2_C128x128;
 }
 
@@ -458,12 +458,15 @@ pulse_status build_layout(pulse_stage* s) {
     for (auto& b : s->eb) { chk(b.cin); chk(b.cout); chk(b.c0); }
     for (auto& b : s->db) { chk(b.cin); chk(b.cout); chk(b.c0); }
     s->k64 = k64;
-    // tile overrides (tuning) index Tile2; they apply on the LDS-DMA path
+    // tile overrides (sweeps and tests) index Tile2; a stage takes those of
+    // its own dtype and channel step
     const int ct = env_int("PULSE_CONV_TILE", -1), wt = env_int("PULSE_WGRAD_TILE", -1);
     s->conv_ksplit_cap = std::max(1, std::min(16, env_int("PULSE_CONV_KSPLIT_MAX", 16)));
     s->no_gnb = env_int("PULSE_NO_GNB", 0) != 0;
     const bool v2 = s->dtype == DT_BF16 && k64;
-    s->conv_tile_force = (v2 && ct >= 0 && ct <= TILE2_CONV_LAST) ? ct : -1;
+    const int first = v2 ? 0 : s->dtype == DT_BF16 ? TILE2_C128x160K32 : TILE2_F64x64;
+    const int last = v2 ? TILE2_CONV_LAST : s->dtype == DT_BF16 ? TILE2_C64x96K32 : TILE2_F32x32;
+    s->conv_tile_force = ct >= first && ct <= last ? ct : -1;
     s->wgrad_tile_force = (v2 && wt >= TILE2_WGRAD_FIRST && wt <= TILE2_WGRAD_LAST) ? wt : -1;
   }
 

@@ -37,9 +37,9 @@ def test_refresh_job_tables(dtype, c):
     _parity(_pair(1, 5, 3, c, 8, 64, dtype, 5), 21, f"refresh-{dtype}")
 
 
-# fp32 tiles (64 x 64, 64 x 32, 32 x 32, a K split) and 32-channel bf16 tiles
-# (64 x 96 with and without a K split, 128 x 128 and 128 x 160, in one and
-# two K splits): remainders in rows and columns, images smaller than a tile
+# fp32 and 32-channel bf16 stages with the tiles and K splits that their rules
+# pick (test_tiles_forced runs each tile whatever the rules say): remainders in
+# rows and columns, images smaller than a tile
 CONV_EDGES = [
     (configs.F32, 1, 3, 5, 96, 32, 1), (configs.F32, 2, 33, 31, 64, 16, 1),
     (configs.F32, 4, 48, 48, 160, 32, 1), (configs.F32, 1, 16, 16, 224, 32, 1),
@@ -78,9 +78,26 @@ def test_small_tiles_forced(monkeypatch, tile, batch, h, w):
     _parity(_pair(batch, h, w, 128, 32, 64, configs.BF16, 1), 24, f"tile{tile}")
 
 
+# the 32-channel tiles (128 x 160, 128 x 128, 64 x 96) and the fp32 ones
+# (64 x 64, 64 x 32, 32 x 32)
+@pytest.mark.parametrize("split", [1, 16])
+@pytest.mark.parametrize("batch,h,w", [(2, 13, 11), (2, 16, 8)])
+@pytest.mark.parametrize("dtype,tile,c", [(configs.BF16, 8, 160), (configs.BF16, 9, 160),
+                                          (configs.BF16, 10, 160), (configs.F32, 11, 96),
+                                          (configs.F32, 12, 96), (configs.F32, 13, 96)])
+def test_tiles_forced(monkeypatch, dtype, tile, c, batch, h, w, split):
+    """Every 32-channel and fp32 tile on every conv of a stage, in one K split
+    (with epilogue statistics where 128-pixel images hold whole tiles) and in
+    the several that such small grids get, on ragged rows and columns."""
+    monkeypatch.setenv("PULSE_CONV_TILE", str(tile))
+    monkeypatch.setenv("PULSE_CONV_KSPLIT_MAX", str(split))
+    _parity(_pair(batch, h, w, c, 32, 64, dtype, 1), 24, f"tile{tile} splits<={split}")
+
+
 # bias gradients inside the weight GEMMs: fewer K-steps than column tiles
-# (8 x 8 images), more, rows past the tile (288 and 448 of 320- and 128-row
-# tiles) and the fp32 loop; their sums go to two biases in decoder blocks
+# (8 x 8 images) and more, the 320-row tile (320 channels; it takes no others,
+# as its rows divide them), 128-row tiles with rows past the end (448 and 288)
+# and the fp32 loop; their sums go to two biases in decoder blocks
 BIAS = [(configs.BF16, 1, 8, 8, 320), (configs.BF16, 2, 33, 20, 448), (configs.BF16, 1, 20, 33, 288),
         (configs.F32, 1, 40, 17, 96)]
 
