@@ -292,11 +292,22 @@ int conv_tile(const pulse_stage* s, int N) {
     return best;
   }
   if (!s->k64) {
-    // 128-row tiles where they fill the GPU (with a K split in two from 200
-    // blocks on) and waste no more than a fifth of their columns; 64 x 96
-    // below (3 x 27 x 45 pixels, 288 -> 288: 24 us against 27 for 128 x 128
-    // and 27 for 128 x 160; 8 x 32 x 32, 480 -> 480: 70 against 55 and 60)
-    const int big = N % 160 == 0 ? TILE2_C128x160K32 : TILE2_C128x128K32;
+    // A 128-row tile where it fills the GPU (with a K split in two from 200
+    // blocks on) and wastes no more than a fifth of its columns, 64 x 96 below.
+    // Where 160 divides N, 128 x 128 serves grids that it does not fill to
+    // seven eighths of two blocks per CU, unless a K split fills the GPU with
+    // 128 x 160 and not with it.  us per conv with 128 x 160, 128 x 128 and
+    // 64 x 96: 8 x 32 x 32 pixels, 480 -> 480: 82, 66, 74; 12 x 32 x 32: 90, 73,
+    // 102; 8 x 32 x 32, 800 -> 800: 138, 128, 200; with the K split 10 x 32 x 32,
+    // 480 -> 480: 68, 73, 98; 8 x 24 x 24, 1120 -> 1120: 131, 162, 224; of more
+    // blocks 11 x 32 x 32, 800 -> 800: 151, 236, 257; 12 x 24 x 24, 1120 -> 1120:
+    // 186, 190, 319; of fewer 6 x 32 x 32, 480 -> 480: 81, 66, 58; 3 x 27 x 45,
+    // 288 -> 288: 54, 43, 32.
+    int big = TILE2_C128x128K32;
+    if (N % 160 == 0) {
+      const long t160 = conv_tiles(s, TILE2_C128x160K32, N), t128 = conv_tiles(s, big, N);
+      if (t128 > 448 || (t160 >= 200 && t160 <= 256 && t128 > 256)) big = TILE2_C128x160K32;
+    }
     const int bn = tile2_info(big).bn;
     const bool wasteful = 5L * ((N + bn - 1) / bn) * bn > 6L * ((N + 95) / 96) * 96;
     return conv_tiles(s, big, N) >= 200 && !wasteful ? big : TILE2_C64x96K32;
