@@ -126,6 +126,35 @@ def test_fp32_weight_gradient_sums():
     assert e < 7e-7, e
 
 
+# LayerNorm backward by width: rows in one to four waves of 512 channels, the
+# last one partly empty (576, 1088, 1600) and full (2048), fewer tokens than
+# blocks allowed and more (576 over 512 blocks); three blocks per half write
+# the column-sum buffers of the first parity twice
+@pytest.mark.parametrize("batch,tokens,heads,n", [(1, 64, 9, 1), (9, 64, 17, 1), (1, 64, 25, 1),
+                                                  (9, 64, 32, 1), (2, 64, 2, 3)])
+def test_layernorm_backward_widths(batch, tokens, heads, n):
+    d = configs._tstage(batch, tokens, 64 * heads, heads, n, n)
+    d["mlp"] = 1
+    log(f"case LayerNorm backward: B={batch} tokens={tokens} heads={heads} blocks={n}+{n}")
+    p, b = synth.make_tstage(d, 28)
+    ref = TO.tstage_run(d, p, b["x"], b["u"], b["g_enc"], b["g_dec"])
+    st = TS.TStage(d)
+    st.set_params(p)
+    dev = {k: st.to_dev(v) for k, v in b.items()}
+    st.zero_grads()
+    got = dict(y_enc=st.forward(TS.ENC, 0, dev["x"]), y_dec=st.forward(TS.DEC, 0, dev["u"]))
+    got["du"] = st.backward(TS.DEC, 0, dev["g_dec"])
+    got["dx"] = st.backward(TS.ENC, 0, dev["g_enc"])
+    got = {k: v.float().cpu().numpy() for k, v in got.items()}
+    got.update(st.grads_dict())
+    want = dict(ref["grads"], **{k: ref[k] for k in ("y_enc", "y_dec", "du", "dx")})
+    errs = {k: rel_l2(got[k], v) for k, v in want.items()}
+    worst = max(errs, key=errs.get)
+    log(f"  worst {worst} = {errs[worst]:.3e}")
+    bad = {k: e for k, e in errs.items() if not e < 2e-2}  # bf16 values, fp32 sums
+    assert not bad, bad
+
+
 # Attention backward with p and ds in registers: from 2048 tokens on, and from
 # 512 blocks on beyond 256 tokens; both lengths end in half a 128-key chunk.
 @pytest.mark.parametrize("batch,tokens,heads", [(1, 2112, 2), (14, 320, 8)])
