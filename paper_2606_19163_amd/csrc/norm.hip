@@ -440,8 +440,7 @@ __global__ __launch_bounds__(256) void k_chan_per_image(const float* partial, in
 constexpr int TX = 8, TY = 32;
 
 __device__ __forceinline__ void chan_totals_block(const float* partial, int rows, int C,
-                                                  int nslot, int cblock, float* acc0,
-                                                  float* dup, float* acc1,
+                                                  int cblock, float* acc0, float* acc1,
                                                   float (&sm)[2][TY][TX]) {
   const int tx = threadIdx.x % TX, ty = threadIdx.x / TX;
   const int c = cblock * TX + tx;
@@ -456,7 +455,7 @@ __device__ __forceinline__ void chan_totals_block(const float* partial, int rows
       for (int k = 0; k < NB; ++k) {
         const int i = i0 + k * TY;
         a[k] = i < rows ? base[(long)i * stride] : 0.f;
-        e[k] = (nslot > 1 && i < rows) ? base[(long)i * stride + C] : 0.f;
+        e[k] = i < rows ? base[(long)i * stride + C] : 0.f;
       }
 #pragma unroll
       for (int k = 0; k < NB; ++k)
@@ -477,9 +476,8 @@ __device__ __forceinline__ void chan_totals_block(const float* partial, int rows
     __syncthreads();
   }
   if (ty == 0 && c < C) {
-    if (acc0) acc0[c] += sm[0][0][tx];
-    if (dup) dup[c] += sm[0][0][tx];
-    if (acc1) acc1[c] += sm[1][0][tx];
+    acc0[c] += sm[0][0][tx];
+    acc1[c] += sm[1][0][tx];
   }
 }
 
@@ -496,8 +494,7 @@ __global__ __launch_bounds__(256, GN_WAVES) void k_gn_bwd_finalize(const float* 
   __shared__ double sm[512];
   const int nbg = g.B * G;
   if ((int)blockIdx.x >= nbg) {
-    chan_totals_block(partial, g.B * rg.chunks, C, 2, blockIdx.x - nbg, dbeta, nullptr, dgamma,
-                      smc);
+    chan_totals_block(partial, g.B * rg.chunks, C, blockIdx.x - nbg, dbeta, dgamma, smc);
     return;
   }
   const int b = blockIdx.x / G, gi = blockIdx.x - b * G;
