@@ -78,10 +78,10 @@ def describe(name, descs):
 # committed FETCH_SIZE/WRITE_SIZE summaries of the conv-mode GEMM launches,
 # each valid for the kernel and planning sources it was taken on
 TRAFFIC_WORKLOADS = {
-    "l64": ["igemm2.hip", "kernels.hpp", "common.hpp", "stage.cpp"],
-    "l32": ["igemm2.hip", "kernels.hpp", "common.hpp", "stage.cpp"],
-    "t768": ["igemm2.hip", "kernels.hpp", "common.hpp", "tstage.cpp"],
-    "t1408": ["igemm2.hip", "kernels.hpp", "common.hpp", "tstage.cpp"],
+    "l64": ["igemm2.hip", "kernels.hpp", "common.hpp", "kpos.hpp", "plan.hpp", "stage.cpp"],
+    "l32": ["igemm2.hip", "kernels.hpp", "common.hpp", "kpos.hpp", "plan.hpp", "stage.cpp"],
+    "t768": ["igemm2.hip", "kernels.hpp", "common.hpp", "kpos.hpp", "plan.hpp", "tstage.cpp"],
+    "t1408": ["igemm2.hip", "kernels.hpp", "common.hpp", "kpos.hpp", "plan.hpp", "tstage.cpp"],
 }
 
 
