@@ -1,24 +1,28 @@
-// Implicit-GEMM convolution, second generation: operand tiles move from
+// Implicit-GEMM convolution and weight gradient: operand tiles move from
 // HBM/L2 to LDS with the LDS-DMA loads of gfx950 (buffer_load ... lds /
 // global_load_lds_dwordx4), so no register staging and no VALU touch the
-// operands on their way to the matrix cores, and two LDS stages overlap the
-// next tile's loads with the current tile's MFMAs.
+// operands on their way to the matrix cores, and two to four LDS stages
+// overlap the next tiles' loads with the current tile's MFMAs.
 //
 // A wave-wide DMA load writes 64 lanes x 16 bytes contiguously (lane i at
 // base + 16 i), so every tile is a dense array of 16-byte chunks and bank
-// conflicts are avoided by XOR-swizzling the chunk index instead of padding.
+// conflicts are avoided by permuting the chunks of a row (XOR in the conv
+// tiles, rotation in the weight gradient's) instead of padding.
 //
-//  * CONV mode (forward, data gradient): tiles are K-contiguous rows of 64
-//    bf16 (128 bytes): A rows are pixels, B rows are output channels.
-//    Fragments are read with ds_read_b128.  Out-of-image taps and rows past
-//    the tile read as zero through out-of-range buffer offsets.
+//  * CONV mode (forward, data gradient): tiles are K-contiguous rows of 64 or
+//    32 bf16, or 32 fp32 (128 or 64 bytes): A rows are pixels, B rows are
+//    output channels.  Fragments are read with ds_read_b128.  Out-of-image
+//    taps and rows past the tile read as zero through out-of-range buffer
+//    offsets.  The waves of a block may form K groups, each with its own
+//    stages, whose sums meet in LDS.
 //  * WGRAD mode: both tiles keep the NHWC order, rows of channels per pixel
-//    ([64 pixels][BM] and [64 pixels][BN]); the MFMA wants 8 consecutive
+//    ([64 pixels][BM] and [64 pixels][BN]).  The bf16 MFMA wants 8 consecutive
 //    pixels per lane, which ds_read_b64_tr_b16 delivers (two per fragment):
 //    within 16 lanes, lane j receives element j%4 of the rows addressed by
-//    lanes 4q + j/4, q = 0..3.  B columns may mix sources within one tile, so
-//    its DMA uses per-lane global addresses; invalid elements point at a
-//    zeroed 16-byte word.
+//    lanes 4q + j/4, q = 0..3.  The fp32 MFMA takes one value per lane, read
+//    with ds_read_b32.  B columns may mix sources within one tile, so its DMA
+//    uses per-lane global addresses; invalid elements point at a zeroed
+//    16-byte word.
 #include <hip/hip_ext.h>
 
 #include <algorithm>
@@ -862,9 +866,11 @@ __global__ __launch_bounds__(C::NT) void igemm2_conv(GemmArgs a) {
 namespace {
 
 // The two A and two B values per lane of four 4-pixel MFMA steps, steps S to
-// S + 3 of the stage: 16 LDS reads and their wait in one block (the compiler
-// must not see the values before they have landed, and cannot tell these
-// reads from the LDS-DMA's targets).
+// S + 3 of the stage: 16 LDS reads in one block, without their wait (the
+// compiler cannot tell them from the LDS-DMA's targets and would wait for
+// that).  The values are in flight until the caller's lgkm_wait; the empty asm
+// that takes them after it keeps every one of their registers reserved until
+// then.
 template <class C, int S>
 __device__ __forceinline__ void rd_f32x16(float (&v)[16], uint32_t a0, uint32_t a1, uint32_t b0,
                                           uint32_t b1) {

@@ -432,7 +432,7 @@ __global__ __launch_bounds__(256) void k_chan_per_image(const float* partial, in
 }
 
 // Channel totals over every image and chunk in one pass: slot 0 is added to
-// acc0 (and dup), slot 1 to acc1.  A 256-thread block holds 8 channels x
+// acc0, slot 1 to acc1.  A 256-thread block holds 8 channels x
 // 32 row lanes; lane y sums the (image, chunk) rows y, y+32, ... (8 loads
 // in flight, added in ascending row order) and the lanes meet in a fixed
 // LDS tree.  Small blocks and few registers: the kernel finds room beside

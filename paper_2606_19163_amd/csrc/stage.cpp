@@ -140,7 +140,6 @@ struct pulse_stage {
   size_t kpart_cap = 0;  // conv K-split partials (elements)
   size_t s_kpart = 0;
   size_t bpart_cap = 0, s_bpart = 0;  // bias-gradient sums of a weight gradient (elements)
- 
   size_t s_chp[2] = {0, 0};  // per-chunk channel sums of dh1 (GN2 backward), by block parity
   int cmax = 0;              // widest channel count of any block
   size_t red_cap = 0;        // floats in each reduction buffer
@@ -328,12 +327,13 @@ long conv_want(const pulse_stage* s) { return s->dtype == DT_F32 ? 256 : 512; }
 
 // K splits of a conv-mode GEMM on that tile: enough blocks to fill the GPU,
 // each split keeping at least 4 K-steps.  The fp32 and the 32-channel tiles
-// pay about 7 us for the partials' finalize and so split only long K: fp32
-// from 128 blocks down to fill the GPU once, 9 or more K-steps per split
-// (1 x 32 x 32, 128 -> 128: 12 us in two splits against 15); 32-channel
-// tiles to two blocks per CU, 18 or more K-steps per split (3 x 27 x 45:
-// 288 -> 96 16 us in four against 28 in one, 96 -> 288, 27 K-steps, 13 us in
-// one against 17 in two).
+// have less work per K-step, so a split must keep more of them to pay for its
+// finalize (2.6 us and the partials' traffic, about 7 us in all for a million
+// outputs in two splits): fp32 from 128 blocks down to fill the GPU once, 9 or
+// more K-steps per split (1 x 32 x 32, 128 -> 128: 12 us in two splits against
+// 15); 32-channel tiles to two blocks per CU, 18 or more K-steps per split
+// (3 x 27 x 45: 288 -> 96 16 us in four against 28 in one, 96 -> 288, 27
+// K-steps, 13 us in one against 17 in two).
 int conv_ksplit(const pulse_stage* s, int tile, int N, int K) {
   const TileInfo ti = tile2_info(tile);
   const long tiles = conv_tiles(s, tile, N);
@@ -1201,10 +1201,10 @@ pulse_status block_backward(pulse_stage* s, int r, const Block& b, const VIn& xi
   char* row = s->row_base(r);
   const int dt = s->dtype;
   pulse_status ps;
-  // Parameter gradients of conv2 / the shortcut (bias sums and the weight
-  // GEMM) only read dout and saved activations: they run on the side stream
-  // while the data-gradient chain continues here.  The side stream has its
-  // own reduction buffer and weight-gradient partials.
+  // Parameter gradients of conv2 / the shortcut (one weight GEMM that also
+  // sums dout's columns for the biases) only read dout and saved activations:
+  // they run on the side stream while the data-gradient chain continues here.
+  // Their partials (weights, biases) are written by that stream alone.
   hipStream_t sd = use_side(s) ? s->side : st;
   // The shortcut's data gradient (a 1x1 conv over dout: short K) runs first
   // and alone: the weight GEMM's blocks leave no room for its own on their
