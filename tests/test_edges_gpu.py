@@ -78,17 +78,18 @@ def test_small_tiles_forced(monkeypatch, tile, batch, h, w):
     _parity(_pair(batch, h, w, 128, 32, 64, configs.BF16, 1), 24, f"tile{tile}")
 
 
-# the 32-channel tiles (128 x 160, 128 x 128, 64 x 96) and the fp32 ones
-# (64 x 64, 64 x 32, 32 x 32)
+# the 32-channel tiles (128 x 160, 128 x 128, 64 x 96), the fp32 ones (64 x 64,
+# 64 x 32, 32 x 32) and the 64-channel ones of small grids
 @pytest.mark.parametrize("split", [1, 16])
 @pytest.mark.parametrize("batch,h,w", [(2, 13, 11), (2, 16, 8)])
 @pytest.mark.parametrize("dtype,tile,c", [(configs.BF16, 8, 160), (configs.BF16, 9, 160),
                                           (configs.BF16, 10, 160), (configs.F32, 11, 96),
-                                          (configs.F32, 12, 96), (configs.F32, 13, 96)])
+                                          (configs.F32, 12, 96), (configs.F32, 13, 96)]
+                         + [(configs.BF16, t, 192) for t in (4, 5, 6, 7)])
 def test_tiles_forced(monkeypatch, dtype, tile, c, batch, h, w, split):
-    """Every 32-channel and fp32 tile on every conv of a stage, in one K split
-    (with epilogue statistics where 128-pixel images hold whole tiles) and in
-    the several that such small grids get, on ragged rows and columns."""
+    """Each of these tiles on every conv of a stage, in one K split (with
+    epilogue statistics where 128-pixel images hold whole tiles) and in the
+    several that such small grids get, on ragged rows and columns."""
     monkeypatch.setenv("PULSE_CONV_TILE", str(tile))
     monkeypatch.setenv("PULSE_CONV_KSPLIT_MAX", str(split))
     _parity(_pair(batch, h, w, c, 32, 64, dtype, 1), 24, f"tile{tile} splits<={split}")
