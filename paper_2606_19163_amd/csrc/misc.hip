@@ -381,8 +381,10 @@ hipError_t RefreshList::flush() {
 
 hipError_t RefreshList::add(RefreshJob job, long blocks) {
   hipError_t e = hipSuccess;
-  // a table or a grid that is full goes first
-  if (set_.n == REFRESH_MAX_JOBS || (long)blocks_ + blocks > 0x7fffffffL) e = flush();
+  // A full table goes first.  Its grid stays below 2^24 blocks, HIP's limit of
+  // 2^32 threads: a 3x3 weight of 8192 by 8192 channels, the largest a stage
+  // takes, has 147456.
+  if (set_.n == REFRESH_MAX_JOBS) e = flush();
   job.first = (int)blocks_;
   set_.job[set_.n++] = job;
   blocks_ += blocks;
