@@ -482,9 +482,9 @@ __global__ __launch_bounds__(C::NT) void igemm2_conv(GemmArgs a) {
   SegRt cur = seg_rt<C::ESZ>(a.seg[0], P);
   int iseg = 0, itap = 0, icb = 0, idy, idx;
   if (kt0 > 0) {  // a later split or K group
-    const KStart k = k_start(kt0, C::BK, KSeg{cur.taps, cur.C}, KSeg{q1.taps, q1.C},
-                             KSeg{q2.taps, q2.C});
-    if (k.seg > 0) select_into(cur, k.seg == 1, q1, q2);
+    const KStart k = k_start(kt0, C::BK, cur, [&](SegRt& s, int i) __attribute__((always_inline)) {
+      select_into(s, i == 1, q1, q2);
+    });
     iseg = k.seg;
     itap = k.tap;
     icb = k.cb;

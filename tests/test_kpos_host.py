@@ -16,6 +16,10 @@ MAIN = r"""
 #include "kpos.hpp"
 using namespace pulse;
 
+struct KSeg {
+  int taps, C;
+};
+
 // segment, tap and channel of K-step kt, found by walking there
 static KStart walk(int kt, int bk, const KSeg (&s)[3]) {
   for (int seg = 0; seg < 3; ++seg)
@@ -40,7 +44,8 @@ int main() {
             const int n = steps < all - ktb ? steps : all - ktb, len = (n + kg - 1) / kg;
             for (int g = 0; g < kg; ++g) {
               const int kt0 = ktb + g * len;
-              const KStart a = k_start(kt0, bk, s[0], s[1], s[2]);
+              KSeg cur = s[0];
+              const KStart a = k_start(kt0, bk, cur, [&](KSeg& c, int i) { c = s[i]; });
               if (kt0 >= all) {
                 ++past;
                 continue;
