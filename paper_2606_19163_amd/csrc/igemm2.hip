@@ -1410,15 +1410,21 @@ __global__ __launch_bounds__(256) void wgrad_finalize(GemmArgs a, int splits, in
 // ---------------------------------------------------------------------------
 
 namespace launch2 {
-// The two tiles of the full-size 3x3 convs start the next stage's DMA before
-// their fragment reads: its latency counts there once more than one round of
-// blocks runs (16 x 48 x 48 x 256 132 us per conv against 142 with the reads
-// first; sampling at 16 x 20 x 20 x 960 1566 against 1664 us, 16 x 19 x 61 x
-// 320 755 against 792, 8 x 64 x 64 x 320 the same).  128 x 192, which only the
-// token GEMMs take, reads first (8192 x 1408 x 5632 124 us against 128).
+// The 128-row tiles start the next stage's DMA before their fragment reads: its
+// latency counts there once more than one round of blocks runs (16 x 48 x 48 x
+// 256 132 us per conv against 142 with the reads first; sampling at 16 x 20 x
+// 20 x 960 1566 against 1664 us, 16 x 19 x 61 x 320 755 against 792, 8 x 64 x
+// 64 x 320 the same).  128 x 192, which only the token GEMMs take: 12288 x 1280
+// x 5120 in 1.3 rounds 185 us against 199; in whole rounds the reads first are
+// up to 3 % faster alone, but not in a stage, where the attention kernel after
+// them, the same code, then takes 140 us instead of 129 (10 x 1472 tokens of
+// 12 heads; the clock seems to sink).  Training iterations, DMA first against
+// reads first: 10 x 1472 tokens x 768 3052 us against 3152, 12 x 1024 x 1280
+// 5169 against 5315, 4 x 4096 x 768 4052 against 4161, 8 x 1024 x 1024 2457
+// against 2467, 8 x 1024 x 1408 4050 against 4023.
 using C2_128x160 = CfgC<128, 160, 64, 80, 2, 64, false, 1, false>;  // 4 waves, two blocks per CU
 using C2_128x128 = CfgC<128, 128, 64, 64, 2, 64, false, 1, false>;  // 4 waves, two blocks per CU
-using C2_128x192 = CfgC<128, 192, 64, 96>;   // 4 waves, two blocks per CU
+using C2_128x192 = CfgC<128, 192, 64, 96, 2, 64, false, 1, false>;  // 4 waves, two blocks per CU
 using C2_64x128S3 = CfgC<64, 128, 32, 64, 3>;  // 4 waves, 3 stages, two blocks per CU
 // grids that do not fill the GPU
 using C2_32x64 = CfgC<32, 64, 16, 32, 4>;
